@@ -8,15 +8,12 @@
 // b_re, b_im) = network(features).  Derivatives of one axis' term:
 //   d/d ml = -2 kl (t - E_q[j]),   d/d kl = (t - ml)^2 - E_q[(j - ml)^2],
 //   d/d b  = kl ln 2 * d/d kl inside the clamp, 0 outside.
-// The training network is float32 without rounding.  Three kernels:
-//   rows:    one thread per row: forward, loss, output gradient, backward to
-//            the hidden layers; stores the activations and deltas it needs;
-//   partial: per chunk of 256 rows, one wavefront forms the weight gradients
-//            dW = sum_r delta_r a_r^T on the matrix cores (float32 16x16x4
-//            MFMAs, the rows as the K dimension; a column of ones in the B
-//            operand gives the biases) and sums the loss;
-//   adam:    one thread per parameter sums the chunks in order and updates
-//            the parameter and the two moment estimates (Adam, Kingma & Ba).
+// The training network is float32 without rounding.  Two kernels:
+//   grad:    every wavefront takes tiles of 16 rows through the forward pass, the loss, the
+//            backward pass and the weight gradients dW = sum_r delta_r a_r^T on the float32
+//            matrix cores, the sums kept in registers; one partial gradient per workgroup;
+//   adam:    sums the partial gradients in a fixed order and updates the parameters and the
+//            two moment estimates (Adam, Kingma & Ba).
 // No atomics: the result does not depend on scheduling.
 #include <cmath>
 
@@ -51,180 +48,315 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
 
 // --------------------------------------------------------------- training
 
-// Per-row workspace record (floats): a0[8] (inputs and the constant 1), a1[64], a2[64], d1[64], d2[64],
-// dout[4], loss[1], 1 pad.
-constexpr int kRecA0 = 0, kRecA1 = 8, kRecA2 = 72, kRecD1 = 136, kRecD2 = 200, kRecDo = 264, kRecL = 268;
-constexpr int kRec = 272;
-constexpr int kChunk = 256;  // rows per partial sum (one wavefront)
-
-__global__ __launch_bounds__(256) void mlp_rows_kernel(const float* __restrict__ w, const float* __restrict__ rows,
-                                                       const int32_t* __restrict__ tgt, int n, float inv_n,
-                                                       float* __restrict__ rec) {
-  __shared__ float W[kMlpParams];
-  for (int i = threadIdx.x; i < kMlpParams; i += blockDim.x) W[i] = w[i];
-  __syncthreads();
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  const float* row = rows + (size_t)r * kTrainRow;
-  float* o = rec + (size_t)r * kRec;
-  float x[kMlpIn];
-#pragma unroll
-  for (int i = 0; i < kMlpIn; ++i) { x[i] = row[i]; o[kRecA0 + i] = x[i]; }
-  o[kRecA0 + 7] = 1.f;
-  float a1[kMlpHid];
-  uint64_t m1 = 0, m2 = 0;
-#pragma unroll
-  for (int j = 0; j < kMlpHid; ++j) {
-    float z = W[kOffB1 + j];
-#pragma unroll
-    for (int i = 0; i < kMlpIn; ++i) z = fmaf(W[kOffW1 + j * kMlpIn + i], x[i], z);
-    m1 |= (z > 0.f ? 1ull : 0ull) << j;
-    a1[j] = fmaxf(z, 0.f);
-    o[kRecA1 + j] = a1[j];
-  }
-  float out[kMlpOut];
-#pragma unroll
-  for (int k = 0; k < kMlpOut; ++k) out[k] = W[kOffB3 + k];
-#pragma unroll
-  for (int j = 0; j < kMlpHid; ++j) {
-    float z = W[kOffB2 + j];
-#pragma unroll
-    for (int i = 0; i < kMlpHid; ++i) z = fmaf(W[kOffW2 + j * kMlpHid + i], a1[i], z);
-    m2 |= (z > 0.f ? 1ull : 0ull) << j;
-    const float a = fmaxf(z, 0.f);
-    o[kRecA2 + j] = a;
-#pragma unroll
-    for (int k = 0; k < kMlpOut; ++k) out[k] = fmaf(W[kOffW3 + k * kMlpHid + j], a, out[k]);
-  }
-  // loss and its gradient with respect to the outputs
-  const float qf = row[10];
-  const int Q = qf >= 16.f ? 16 : (qf >= 2.f ? (int)qf : 2);
-  const float kap = row[9];
-  float dout[kMlpOut];
-  float loss = 0.f;
-  for (int p = 0; p < 2; ++p) {
-    const int t = tgt[2 * (size_t)r + p];
-    const float b = fminf(fmaxf(out[2 + p], -4.f), 4.f);
-    const float ml = row[7 + p] + out[p];
-    const float kl = kap * exp2f(b);
-    float mx = -INFINITY;
-    for (int j = 0; j < Q; ++j) { const float d = j - ml; mx = fmaxf(mx, -kl * d * d); }
-    float Z = 0.f, Ej = 0.f, Ed2 = 0.f;
-    for (int j = 0; j < Q; ++j) {
-      const float d = j - ml;
-      const float e = expf(-kl * d * d - mx);
-      Z += e; Ej += e * j; Ed2 += e * d * d;
-    }
-    Ej /= Z; Ed2 /= Z;
-    const float dt = t - ml;
-    loss += kl * dt * dt + mx + logf(Z);
-    dout[p] = -2.f * kl * (t - Ej);
-    const float dk = dt * dt - Ed2;
-    dout[2 + p] = (fabsf(out[2 + p]) < 4.f) ? dk * kl * 0.69314718055994531f : 0.f;
-  }
-#pragma unroll
-  for (int k = 0; k < kMlpOut; ++k) { dout[k] *= inv_n; o[kRecDo + k] = dout[k]; }
-  o[kRecL] = loss * inv_n;
-  // backward to the hidden layers
-  float d2[kMlpHid];
-#pragma unroll
-  for (int j = 0; j < kMlpHid; ++j) {
-    float v = 0.f;
-#pragma unroll
-    for (int k = 0; k < kMlpOut; ++k) v = fmaf(dout[k], W[kOffW3 + k * kMlpHid + j], v);
-    d2[j] = ((m2 >> j) & 1ull) ? v : 0.f;
-    o[kRecD2 + j] = d2[j];
-  }
-#pragma unroll
-  for (int i = 0; i < kMlpHid; ++i) {
-    float v = 0.f;
-#pragma unroll
-    for (int j = 0; j < kMlpHid; ++j) v = fmaf(d2[j], W[kOffW2 + j * kMlpHid + i], v);
-    o[kRecD1 + i] = ((m1 >> i) & 1ull) ? v : 0.f;
-  }
-}
-
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// One wavefront per chunk of kChunk rows.  v_mfma_f32_16x16x4f32 lane layout (checked on the device):
-// A (16 x 4) lane l holds A[l % 16][l / 16], B (4 x 16) lane l holds B[l / 16][l % 16], and register j of
-// the accumulator holds D[4 (l / 16) + j][l % 16].  With 4 rows per step (row r0 + l / 16):
-//   dW2 (64 x 64, bias column): A = d2 tile, B = a1 tile or the ones column;
-//   dW1 (64 x 8 = W1 | b1):     A = d1 tile, B = a0 (its 8th entry is the constant 1);
-//   dW3 (4 x 64, bias column):  A = dout (rows 0..3 of the tile), B = a2 tile or the ones column.
-__global__ __launch_bounds__(64) void mlp_partial_kernel(const float* __restrict__ rec, int n, float* __restrict__ part) {
-  const int l = threadIdx.x, c = l & 15, q = l >> 4;
-  const int r0 = blockIdx.x * kChunk;
-  f32x4 g2[4][5], g1[4], g3[5];
-  const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    g1[t] = z;
-#pragma unroll
-    for (int u = 0; u < 5; ++u) g2[t][u] = z;
-  }
-#pragma unroll
-  for (int u = 0; u < 5; ++u) g3[u] = z;
-  float ls = 0.f;
-  for (int kk = 0; kk < kChunk; kk += 4) {
-    const int r = r0 + kk + q;
-    const bool ok = r < n;
-    const float* o = rec + (size_t)(ok ? r : 0) * kRec;
-    float a1v[4], a2v[4], d1v[4], d2v[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      a1v[t] = ok ? o[kRecA1 + 16 * t + c] : 0.f;
-      a2v[t] = ok ? o[kRecA2 + 16 * t + c] : 0.f;
-      d1v[t] = ok ? o[kRecD1 + 16 * t + c] : 0.f;
-      d2v[t] = ok ? o[kRecD2 + 16 * t + c] : 0.f;
-    }
-    const float a0v = (ok && c < 8) ? o[kRecA0 + c] : 0.f;
-    const float dov = (ok && c < kMlpOut) ? o[kRecDo + c] : 0.f;
-    const float one = (ok && c == 0) ? 1.f : 0.f;
-    if (ok && c == 0) ls += o[kRecL];
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-#pragma unroll
-      for (int it = 0; it < 4; ++it) g2[jt][it] = __builtin_amdgcn_mfma_f32_16x16x4f32(d2v[jt], a1v[it], g2[jt][it], 0, 0, 0);
-      g2[jt][4] = __builtin_amdgcn_mfma_f32_16x16x4f32(d2v[jt], one, g2[jt][4], 0, 0, 0);
-      g1[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(d1v[jt], a0v, g1[jt], 0, 0, 0);
-    }
-#pragma unroll
-    for (int it = 0; it < 4; ++it) g3[it] = __builtin_amdgcn_mfma_f32_16x16x4f32(dov, a2v[it], g3[it], 0, 0, 0);
-    g3[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(dov, one, g3[4], 0, 0, 0);
-  }
-  float* out = part + (size_t)blockIdx.x * (kMlpParams + 1);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 4 * q + j;   // row of the accumulator tile
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-      const int u = 16 * jt + row;   // hidden unit
-#pragma unroll
-      for (int it = 0; it < 4; ++it) out[kOffW2 + u * kMlpHid + 16 * it + c] = g2[jt][it][j];
-      if (c == 0) out[kOffB2 + u] = g2[jt][4][j];
-      if (c < kMlpIn) out[kOffW1 + u * kMlpIn + c] = g1[jt][j];
-      if (c == kMlpIn) out[kOffB1 + u] = g1[jt][j];
-    }
-    if (row < kMlpOut) {
-#pragma unroll
-      for (int it = 0; it < 4; ++it) out[kOffW3 + row * kMlpHid + 16 * it + c] = g3[it][j];
-      if (c == 0) out[kOffB3 + row] = g3[4][j];
-    }
-  }
-  // the loss: the four lanes (c == 0) of the four row slots, in a fixed order
-  ls += __shfl_xor(ls, 16);
-  ls += __shfl_xor(ls, 32);
-  if (l == 0) out[kMlpParams] = ls;
+constexpr int kTrainTile = 16;    // rows per wavefront tile
+constexpr int kTrainWaves = 4;    // wavefronts per workgroup of the gradient kernel
+constexpr int kTrainWgs = 256;    // its largest grid: one workgroup per CU, one wavefront per SIMD
+constexpr int kPart = 4992;       // floats of one workgroup's partial gradient (4932 parameters, loss, pad)
+static_assert(kMlpParams + 1 <= kPart, "partial record");
+constexpr int kW2Ld = 68;         // LDS row stride of W2 and of the transposed tiles: 16 B reads of 4 columns and
+                                  // 4 B reads of 16 columns x 4 rows each touch every bank once
+
+// Workgroups of the gradient kernel for n rows (also the number of partial gradients).
+inline int train_wgs(int n) {
+  const int tiles = (n + kTrainTile - 1) / kTrainTile, wgs = (tiles + kTrainWaves - 1) / kTrainWaves;
+  return wgs < kTrainWgs ? wgs : kTrainWgs;
 }
 
-__global__ __launch_bounds__(256) void mlp_adam_kernel(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                                                       const float* __restrict__ part, int chunks, int step, float lr,
-                                                       float* __restrict__ loss, float* __restrict__ grad) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > kMlpParams) return;
+// Accumulators of one wavefront: the weight gradients as 16 x 16 tiles (register j of lane (q, c), q = lane / 16,
+// c = lane % 16: row 4 q + j, column c), b2's as per-lane sums over the lane's rows, b3's and the loss.
+struct GradAcc {
+  f32x4 g2[4][4], g1[4], g3[4], b2[4], b3;
+  float loss;
+};
+constexpr int kAccRegs = 16 * 4 + 3 * 16 + 4 + 1;
+
+// every accumulator register v, numbered, becomes f(number, v)
+template <typename F>
+__device__ __forceinline__ void for_acc(GradAcc& a, F&& f) {
+  int i = 0;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a.g2[t][u][j] = f(i++, a.g2[t][u][j]);
+      a.g1[t][j] = f(i++, a.g1[t][j]);
+      a.g3[t][j] = f(i++, a.g3[t][j]);
+      a.b2[t][j] = f(i++, a.b2[t][j]);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) a.b3[j] = f(i++, a.b3[j]);
+  a.loss = f(i++, a.loss);
+}
+
+// Loss, forward, backward and weight gradients of the rows, all on the float32 matrix cores
+// (v_mfma_f32_16x16x4f32: A (16 x 4) lane l holds A[l % 16][l / 16], B (4 x 16) lane l holds B[l / 16][l % 16],
+// register j of the accumulator D[4 (l / 16) + j][l % 16]).  A wavefront takes 16 rows at a time as the columns of
+// every product: lane (q, c) then holds hidden units 16 t + 4 q + j of row c, and the next layer's K step (t, j)
+// uses exactly those registers as its B operand (weights read in that K order), so that forward and backward
+// exchange nothing between lanes.  The weight gradients contract over the rows; their operands are the transposed
+// tiles, which pass through LDS (two 16 x 64 tiles per wavefront).  236 products per tile, 8 passes each: the
+// products of 65 536 rows need 13 us at the float32 matrix rate.  Measured 39-41 us (40 % of a wave's cycles in
+// products, 35 % waiting on LDS and on dependent products with one wavefront per SIMD, which the 117 accumulator
+// registers ask for); nothing per row goes to memory: one thread per row that wrote its activations out, and a
+// second kernel that read them back for the weight gradients, took 140 us.
+__global__ __launch_bounds__(64 * kTrainWaves) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void mlp_grad_kernel(const float* __restrict__ w, const float* __restrict__ rows, const int32_t* __restrict__ tgt,
+                     int n, float inv_n, float* __restrict__ part) {
+  // W2, then per wavefront two transposed tiles, the inputs and the output gradients; reused for the
+  // sum over the workgroup's wavefronts
+  constexpr int kWaveLds = 2 * kTrainTile * kW2Ld + kTrainTile * 8 + kTrainTile * 4;
+  constexpr int kLds = kMlpHid * kW2Ld + kTrainWaves * kWaveLds;
+  constexpr int kSlots = 2 * kAccRegs * 64;
+  __shared__ __attribute__((aligned(16))) float lds[kLds > kSlots ? kLds : kSlots];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, q = lane >> 4;
+  float* W2 = lds;
+  float* bufA = lds + kMlpHid * kW2Ld + wave * kWaveLds;
+  float* bufB = bufA + kTrainTile * kW2Ld;
+  float* xs = bufB + kTrainTile * kW2Ld;
+  float* ds = xs + kTrainTile * 8;
+  for (int i = tid; i < kMlpHid * kMlpHid; i += 64 * kTrainWaves) W2[(i >> 6) * kW2Ld + (i & 63)] = w[kOffW2 + i];
+  // first-layer weights and bias, [unit 16 t + c][input 4 s + q]; third layer in the K order of the lane's
+  // units, its 4 rows repeated in every group of 4 so that each lane group gets all 4 outputs; and its transpose
+  float w1[4][2], w3[4][4], w3t[4];
+  f32x4 b2v[4], b3v;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int u = 16 * t + c;
+    w1[t][0] = w[kOffW1 + u * kMlpIn + q];
+    w1[t][1] = q < 3 ? w[kOffW1 + u * kMlpIn + 4 + q] : w[kOffB1 + u];
+    w3t[t] = w[kOffW3 + q * kMlpHid + u];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      w3[t][j] = w[kOffW3 + (c & 3) * kMlpHid + 16 * t + 4 * q + j];
+      b2v[t][j] = w[kOffB2 + 16 * t + 4 * q + j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) b3v[j] = w[kOffB3 + j];
+  __syncthreads();
+  GradAcc acc;
+  for_acc(acc, [](int, float) { return 0.f; });
+
+  const int tiles = (n + kTrainTile - 1) / kTrainTile;
+  // the lane's part of a row: inputs q and 4 + q, and the centre, precision, level count and target of axis q % 2
+  struct RowIn { float x0, x1, mu, kap, qf; int t; };
+  auto load_row = [&](int tile) {
+    const int r = tile * kTrainTile + c;
+    const bool ok = r < n;
+    const float* row = rows + (size_t)(ok ? r : 0) * kTrainRow;
+    RowIn v;
+    v.x0 = row[q]; v.x1 = row[4 + q]; v.mu = row[7 + (q & 1)]; v.kap = row[9]; v.qf = row[10];
+    v.t = tgt[2 * (size_t)(ok ? r : 0) + (q & 1)];
+    if (!ok) v = RowIn{0.f, 0.f, 0.f, 1.f, 2.f, 0};
+    if (q == 3) v.x1 = 1.f;
+    return v;
+  };
+  RowIn next = load_row(blockIdx.x * kTrainWaves + wave);
+  for (int tile = blockIdx.x * kTrainWaves + wave; tile < tiles; tile += gridDim.x * kTrainWaves) {
+    const bool ok = tile * kTrainTile + c < n;
+    const float x0 = next.x0, x1 = next.x1, mup = next.mu, kap = next.kap, qf = next.qf;
+    const int tg = next.t;
+    next = load_row(tile + gridDim.x * kTrainWaves);   // in flight during this tile (past the end: row 0, unused)
+    // forward
+    f32x4 a1[4], a2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      f32x4 z = {0.f, 0.f, 0.f, 0.f};
+      z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[t][0], x0, z, 0, 0, 0);
+      z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[t][1], x1, z, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a1[t][j] = fmaxf(z[j], 0.f);
+      a2[t] = b2v[t];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      f32x4 av[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) av[t] = *(const f32x4*)(W2 + (16 * t + c) * kW2Ld + 16 * s + 4 * q);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t][j], a1[s][j], a2[t], 0, 0, 0);
+    }
+    f32x4 o[2] = {b3v, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        a2[s][j] = fmaxf(a2[s][j], 0.f);
+        o[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3[s][j], a2[s][j], o[j & 1], 0, 0, 0);
+      }
+    const f32x4 out = o[0] + o[1];
+    // loss and its gradient with respect to the outputs: lane group q takes axis q % 2 of its row
+    const int Q = qf >= 16.f ? 16 : (qf >= 2.f ? (int)qf : 2);
+    const bool im = q & 1;
+    const float oD = im ? out[1] : out[0], ob = im ? out[3] : out[2];
+    const float ml = mup + oD, kl = kap * exp2f(fminf(fmaxf(ob, -4.f), 4.f));
+    // the largest logit is the nearest level's; lane groups q and q ^ 2 share an axis and take half its levels each
+    const float d0 = fminf(fmaxf(rintf(ml), 0.f), (float)(Q - 1)) - ml, mx = -kl * d0 * d0;
+    float Z = 0.f, Ej = 0.f, Ed2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int j = 2 * i + (q >> 1);
+      const float d = j - ml;
+      const float e = j < Q ? expf(-kl * d * d - mx) : 0.f;
+      Z += e; Ej += e * j; Ed2 += e * d * d;
+      if (i == 3 && !__any(Q > 8)) break;
+    }
+    Z += __shfl_xor(Z, 32); Ej += __shfl_xor(Ej, 32); Ed2 += __shfl_xor(Ed2, 32);
+    Ej /= Z; Ed2 /= Z;
+    const float dt = tg - ml;
+    const float sc = ok ? inv_n : 0.f;
+    float ls = kl * dt * dt + mx + logf(Z);
+    float dD = -2.f * kl * (tg - Ej);
+    float db = (fabsf(ob) < 4.f) ? (dt * dt - Ed2) * kl * 0.69314718055994531f : 0.f;
+    ls = ok ? ls * sc : 0.f;
+    dD = ok ? dD * sc : 0.f;
+    db = ok ? db * sc : 0.f;
+    const float pD = __shfl_xor(dD, 16), pb = __shfl_xor(db, 16);
+    const f32x4 dout = {im ? pD : dD, im ? dD : pD, im ? pb : db, im ? db : pb};
+    if (q < 2) acc.loss += ls;
+    if (q == 0) acc.b3 += dout;
+    // backward to the hidden layers
+    f32x4 d1[4], d2[4];
+    const float dq = q == 0 ? dout[0] : (q == 1 ? dout[1] : (q == 2 ? dout[2] : dout[3]));
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+      d2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3t[t], dq, z, 0, 0, 0);
+      d1[t] = z;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) d2[t][j] = a2[t][j] > 0.f ? d2[t][j] : 0.f;
+      acc.b2[t] += d2[t];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float* wr = W2 + (16 * s + 4 * q + j) * kW2Ld + c;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[16 * t], d2[s][j], d1[t], 0, 0, 0);
+      }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) d1[t][j] = a1[t][j] > 0.f ? d1[t][j] : 0.f;
+    // weight gradients: the tiles transposed to [row][unit] (LDS of this wavefront alone: its own order suffices)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      *(f32x4*)(bufA + c * kW2Ld + 16 * t + 4 * q) = a1[t];
+      *(f32x4*)(bufB + c * kW2Ld + 16 * t + 4 * q) = d2[t];
+    }
+    xs[c * 8 + q] = x0;
+    xs[c * 8 + 4 + q] = x1;
+    if (q == 0) *(f32x4*)(ds + c * 4) = dout;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      float av[4], dv[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        av[t] = bufA[(4 * s + q) * kW2Ld + 16 * t + c];
+        dv[t] = bufB[(4 * s + q) * kW2Ld + 16 * t + c];
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc.g2[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[t], av[u], acc.g2[t][u], 0, 0, 0);
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      *(f32x4*)(bufA + c * kW2Ld + 16 * t + 4 * q) = a2[t];
+      *(f32x4*)(bufB + c * kW2Ld + 16 * t + 4 * q) = d1[t];
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      float av[4], dv[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        av[t] = bufA[(4 * s + q) * kW2Ld + 16 * t + c];
+        dv[t] = bufB[(4 * s + q) * kW2Ld + 16 * t + c];
+      }
+      const float xv = c < 8 ? xs[(4 * s + q) * 8 + (c & 7)] : 0.f;
+      const float ov = c < kMlpOut ? ds[(4 * s + q) * 4 + (c & 3)] : 0.f;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        acc.g1[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[t], xv, acc.g1[t], 0, 0, 0);
+        acc.g3[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ov, av[t], acc.g3[t], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // sum over the wavefronts in a fixed order, (0 + 2) + (1 + 3), through two register-image slots
+  __syncthreads();
+  float* slot = lds + (wave & 1) * kAccRegs * 64 + lane;
+  if (wave >= 2) for_acc(acc, [&](int i, float v) { return slot[i * 64] = v; });
+  __syncthreads();
+  if (wave < 2) for_acc(acc, [&](int i, float v) { return v + slot[i * 64]; });
+  __syncthreads();
+  if (wave == 1) for_acc(acc, [&](int i, float v) { return slot[i * 64] = v; });
+  __syncthreads();
+  if (wave != 0) return;
+  slot += kAccRegs * 64;
+  for_acc(acc, [&](int i, float v) { return v + slot[i * 64]; });
+  // b2 and b3 over the 16 rows of a tile's lanes, the loss over all lanes
+#pragma unroll
+  for (int s = 1; s < 16; s <<= 1) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc.b2[t][j] += __shfl_xor(acc.b2[t][j], s);
+      acc.b3[j] += __shfl_xor(acc.b3[j], s);
+    }
+    acc.loss += __shfl_xor(acc.loss, s);
+  }
+  acc.loss += __shfl_xor(acc.loss, 16);
+  float* out = part + (size_t)blockIdx.x * kPart;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int u = 16 * t + 4 * q + j;   // hidden unit
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[kOffW2 + u * kMlpHid + 16 * i + c] = acc.g2[t][i][j];
+      if (c < kMlpIn) out[kOffW1 + u * kMlpIn + c] = acc.g1[t][j];
+      if (c == kMlpIn) out[kOffB1 + u] = acc.g1[t][j];
+      if (c == 0) out[kOffB2 + u] = acc.b2[t][j];
+      if (q == 0) out[kOffW3 + j * kMlpHid + 16 * t + c] = acc.g3[t][j];
+    }
+    if (lane == 0) out[kOffB3 + j] = acc.b3[j];
+  }
+  if (lane == 0) out[kMlpParams] = acc.loss;
+}
+
+// Adam on 64 parameters per workgroup.  Its 8 wavefronts each sum every eighth partial gradient (the sums then
+// meet in LDS in a fixed order): with one thread per parameter alone, the 256 dependent trips to the partials took
+// 63 us; 78 workgroups x 8 slices with 8 loads in flight are bound by the latency of 4 trips.
+constexpr int kAdamSlices = 8;
+__global__ __launch_bounds__(64 * kAdamSlices) void mlp_adam_kernel(float* __restrict__ w, float* __restrict__ m,
+                                                                    float* __restrict__ v, const float* __restrict__ part,
+                                                                    int chunks, int step, float lr, float* __restrict__ loss,
+                                                                    float* __restrict__ grad) {
+  __shared__ float sums[kAdamSlices][64];
+  const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;
   float g = 0.f;
-  for (int c = 0; c < chunks; ++c) g += part[(size_t)c * (kMlpParams + 1) + p];
+  const float* src = part + (size_t)sl * kPart + p;
+#pragma unroll 8
+  for (int k = sl; k < chunks; k += kAdamSlices) {
+    g += *src;
+    src += (size_t)kAdamSlices * kPart;
+  }
+  sums[sl][lane] = g;
+  __syncthreads();
+  if (sl != 0 || p > kMlpParams) return;
+#pragma unroll
+  for (int k = 1; k < kAdamSlices; ++k) g += sums[k][lane];
   if (p == kMlpParams) {
     if (loss) loss[0] = g;
     return;
@@ -264,8 +396,7 @@ dmala_status dmala_mlp_forward(const float* weights, const float* rows, int32_t 
 
 size_t dmala_mlp_train_workspace_size(int32_t n_rows) {
   if (n_rows < 1) return 0;
-  const size_t chunks = (n_rows + kChunk - 1) / kChunk;
-  return round_up((size_t)n_rows * kRec * 4, 256) + round_up(chunks * (kMlpParams + 1) * 4, 256);
+  return round_up((size_t)train_wgs(n_rows) * kPart * sizeof(float), 256);
 }
 
 dmala_status dmala_mlp_train_step(float* weights, float* adam_m, float* adam_v, int32_t step, float lr,
@@ -280,19 +411,14 @@ dmala_status dmala_mlp_train_step(float* weights, float* adam_m, float* adam_v, 
   if (workspace_bytes < need) return fail(DMALA_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", workspace_bytes, need);
   if (((uintptr_t)workspace & 255) != 0) return fail(DMALA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   hipStream_t s = (hipStream_t)stream;
-  float* rec = (float*)workspace;
-  float* part = (float*)((unsigned char*)workspace + round_up((size_t)n_rows * kRec * 4, 256));
-  const int chunks = (n_rows + kChunk - 1) / kChunk;
-  hipLaunchKernelGGL(mlp_rows_kernel, dim3((n_rows + 255) / 256), dim3(256), 0, s, weights, rows, targets, n_rows,
-                     1.0f / (float)n_rows, rec);
+  float* part = (float*)workspace;
+  const int wgs = train_wgs(n_rows);
+  hipLaunchKernelGGL(mlp_grad_kernel, dim3(wgs), dim3(64 * kTrainWaves), 0, s, weights, rows, targets, n_rows,
+                     1.0f / (float)n_rows, part);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "mlp rows launch");
-  const int pb = (kMlpParams + 1 + 255) / 256;
-  hipLaunchKernelGGL(mlp_partial_kernel, dim3(chunks), dim3(64), 0, s, rec, n_rows, part);
-  e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "mlp partial launch");
-  hipLaunchKernelGGL(mlp_adam_kernel, dim3(pb), dim3(256), 0, s, weights, adam_m, adam_v, part, chunks, step, lr, loss,
-                     grad);
+  if (e != hipSuccess) return hip_fail(e, "mlp gradient launch");
+  hipLaunchKernelGGL(mlp_adam_kernel, dim3((kMlpParams + 1 + 63) / 64), dim3(64 * kAdamSlices), 0, s, weights, adam_m, adam_v,
+                     part, wgs, step, lr, loss, grad);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "mlp adam launch");
   g_err.clear();

@@ -112,6 +112,28 @@ def test_training_step_matches_the_oracle():
         assert d.max() <= 2 * 2e-3 * step
 
 
+@pytest.mark.parametrize("R", [1, 15, 17, 64, 65, 1000, 16384, 16401])
+def test_training_gradient_at_tile_edges(R):
+    """Row counts around a wavefront's tile (16), a workgroup's (64) and the full grid's (16384).
+
+    Tolerance: every gradient entry passes five float32 sums of at most 64 terms (error about
+    sqrt(64) 2^-24 each, 2.4e-6 together) and one over the rows in partial sums; a hidden unit whose
+    input is within rounding of 0 may take the other side of the ReLU, about 128 R 1e-6 / R of the
+    terms.  2-norm within 2e-5 of the oracle's, the loss within 1e-5."""
+    import torch
+    import paper_2407_06042_amd as dm
+    P = _params(5, scale=3.0)
+    rows, tgt = _train_set(R, 9)
+    tr = dm.MlpTrainer(_dev(P), lr=2e-3)
+    loss = float(tr.step(torch.from_numpy(rows.astype(np.float32)).cuda(),
+                         torch.from_numpy(tgt.astype(np.int32)).cuda()).cpu().numpy()[0])
+    g = tr.grad.cpu().numpy().astype(np.float64)
+    Lo, Go = ol.training_loss(P, rows[:, :7], rows[:, 7:9], rows[:, 9], rows[:, 10].astype(int), tgt, grad=True)
+    go = ol.flatten(Go)
+    assert abs(loss - Lo) < 1e-5 * max(1.0, abs(Lo))
+    assert np.linalg.norm(g - go) < 2e-5 * np.linalg.norm(go)
+
+
 def test_training_rows_match_the_oracle_features():
     import torch
     import paper_2407_06042_amd as dm

@@ -354,8 +354,12 @@ constexpr int cx_lds_halves(int rt, bool win) { return rt <= 8 ? 7 : (win ? 3 : 
 // of being staged in LDS.
 // FULL: the instance has no padding dimensions (N == Npad), so that no dimension needs the
 // padding masks (the caller checks; the results are the same either way).
+// HALF (32 dimensions, one wave): the instance has at most 16 real dimensions, so that the second row
+// tile holds only padding.  A padding dimension keeps its initial level, its centre and gradient, and
+// enters nothing but the log normalisers, with a constant weight sum: the wave leaves the tile out and
+// multiplies by those constants where the full loop would (bit for bit the full loop's results).
 template <typename Real, int RTW, int WD, bool MG, int Q, int PM, bool EVAL, int WIN, int KND, bool CX = false,
-          bool FULL = false>
+          bool FULL = false, bool HALF = false>
 __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int inst, const int cgy) {
   constexpr bool F64 = std::is_same<Real, double>::value;
   constexpr bool LRN = KND == 1;   // plain/learned kernel mixture
@@ -366,8 +370,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
   static_assert(!CX || (!F64 && !LRN && RTW % 4 == 0 && (MG ? RTW * WD >= 8 : RTW * WD == 4)),
                 "complex-plane matrices: float, whole 32-antenna K blocks per wave, from L2 or (64 dimensions) LDS");
   static_assert(WD == 1 || RTW % 2 == 0, "dimension-split waves own whole K blocks");
+  static_assert(!HALF || (RTW == 2 && WD == 1 && !MG && !CX && !F64 && KND == 0 && !EVAL), "HALF: the 32-dimension float layout");
   constexpr int RT = RTW * WD;
-  constexpr int D = 4 * RTW;
+  constexpr int RTA = HALF ? 1 : RTW;   // row tiles (groups) the wave works on
+  constexpr int D = 4 * RTA;
   constexpr int KB = RT / 2;
   constexpr int KBW = RTW / 2;
   constexpr int NPP = p_passes(PM);
@@ -706,14 +712,17 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int d = (2 * kb + (q >> 1)) * 4 + 2 * (q & 1);   // elements 2q, 2q + 1
-          wh[q] = lv_pair<QM1>(k[d], k[d + 1]);
+          // (the padding tile's columns of the matrices are zero: any finite value will do)
+          if constexpr (HALF) wh[q] = q < 2 ? lv_pair<QM1>(k[d], k[d + 1]) : 0u;
+          else wh[q] = lv_pair<QM1>(k[d], k[d + 1]);
         }
         __builtin_memcpy(&bh[wd * KBW + kb], wh, 16);
         if constexpr (PM == PM_BF16X1) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const int d = (2 * kb + (j >> 2)) * 4 + (j & 3);
-            bb[wd * KBW + kb][j] = (__bf16)(float)(2 * k[d] - QM1);
+            if constexpr (HALF) bb[wd * KBW + kb][j] = j < 4 ? (__bf16)(float)(2 * k[d] - QM1) : (__bf16)0.f;
+            else bb[wd * KBW + kb][j] = (__bf16)(float)(2 * k[d] - QM1);
           }
         }
       }
@@ -740,7 +749,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         else return smem + off;
       };
 #pragma unroll
-      for (int rt = 0; rt < RTW; ++rt) {
+      for (int rt = 0; rt < RTA; ++rt) {
         const int rtg = rt0 + rt;
         f32x4 e = {0.f, 0.f, 0.f, 0.f};
         if constexpr (MG && RT >= 8) {
@@ -987,11 +996,22 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
     const uint32_t key0 = a.key0, key1 = a.key1;
     // initial state from the t = 0 words
 #pragma unroll
-    for (int rt = 0; rt < RTW; ++rt) {
+    for (int rt = 0; rt < RTA; ++rt) {
       uint32_t c[4] = {(uint32_t)(gdim(rt) >> 2), 0u, (uint32_t)chain, rctr};
       philox4x32_10<true>(c, key0, key1);
 #pragma unroll
       for (int i = 0; i < 4; ++i) kc[rt * 4 + i] = Real((int)(((uint64_t)(c[i] >> 8) * Q) >> 24));
+    }
+    // HALF: the padding tile's constant weight sums
+    Real zpad[HALF ? 4 : 1];
+    if constexpr (HALF) {
+      uint32_t c[4] = {(uint32_t)(16 + 4 * h) >> 2, 0u, (uint32_t)chain, rctr};
+      philox4x32_10<true>(c, key0, key1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        Real b2;
+        norm_parts<Q, WIN, W, TAB>(Real((int)(((uint64_t)(c[i] >> 8) * Q) >> 24)), kL, wc, zpad[i], b2);
+      }
     }
     Real muL[D], kLL[D];  // cached learned proposal (LRN)
     Real lzs = 0;         // sum of the lane's log2 normalisers at the current state (plain kernel)
@@ -1003,6 +1023,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       if constexpr (KND == 0) {
 #pragma unroll
         for (int d = 0; d < D; ++d) lzs += log2_norm<Q, WIN, W, TAB>(mu[d], kL, wc);
+        if constexpr (HALF) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) lzs += lg2(zpad[i]);
+        }
       }
     }
     // E(x) = ||y||^2 + x^T g - z^T x = ||y||^2 + (eunit/2) sum_n lv_n (eg_n - ez_n)
@@ -1029,9 +1053,9 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       }
       return (uint32_t)v[0] | ((uint32_t)v[1] << 8) | ((uint32_t)v[2] << 16) | ((uint32_t)v[3] << 24);
     };
-    uint32_t kbest[RTW];
+    uint32_t kbest[RTA];
 #pragma unroll
-    for (int rt = 0; rt < RTW; ++rt) kbest[rt] = pack4(rt);
+    for (int rt = 0; rt < RTA; ++rt) kbest[rt] = pack4(rt);
     int nacc = 0;
     uint32_t abits = 0;
     const size_t trow = (size_t)rid * a.C + (live ? chain : 0);
@@ -1040,19 +1064,19 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
     // depend on the chain: on the one-wave layouts with up to 4 row tiles the words of
     // t + 1 are generated while the contraction of t runs on the matrix cores (elsewhere
     // the registers they would hold meanwhile are not free).
-    uint32_t w[RTW][4];
+    uint32_t w[RTA][4];
     auto word_block = [&](int rt, int tt) {
       w[rt][0] = (uint32_t)(gdim(rt) >> 2); w[rt][1] = (uint32_t)tt; w[rt][2] = (uint32_t)chain; w[rt][3] = rctr;
       philox4x32_10<true>(w[rt], key0, key1);
     };
     if constexpr (PIPE) {
 #pragma unroll
-      for (int rt = 0; rt < RTW; ++rt) word_block(rt, 1);
+      for (int rt = 0; rt < RTA; ++rt) word_block(rt, 1);
     }
     for (int t = 1; t <= a.T; ++t) {
       if constexpr (!PIPE) {
 #pragma unroll
-        for (int rt = 0; rt < RTW; ++rt) word_block(rt, t);
+        for (int rt = 0; rt < RTA; ++rt) word_block(rt, t);
       }
       // kernel choice of the mixture (LRN): learned unless the uniform from the
       // low bytes of words 4, 5, 6 falls below eps; every lane of the chain
@@ -1134,6 +1158,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           tr += t0 * t0;
           T2 -= (Real(kp[d]) - Real(kc[d])) * (eg[d] + egp[d]);
         }
+        if constexpr (HALF) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) zp *= zpad[i];
+        }
         lzps = lg2(zp) - kL * bs;
         S -= kL * tr + lzps;
       }
@@ -1170,7 +1198,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       if (E < Ebest) {
         Ebest = E;
 #pragma unroll
-        for (int rt = 0; rt < RTW; ++rt) kbest[rt] = pack4(rt);
+        for (int rt = 0; rt < RTA; ++rt) kbest[rt] = pack4(rt);
       }
       if (a.trace_accept) {
         abits |= (acc ? 1u : 0u) << ((t - 1) & 31);
@@ -1211,7 +1239,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         for (int d = 0; d < D; ++d) egs[dim_of(d)] = valid[d] ? (float)eg[d] : 0.0f;
       }
 #pragma unroll
-      for (int rt = 0; rt < RTW; ++rt) {
+      for (int rt = 0; rt < RTA; ++rt) {
         const int n0 = gdim(rt);
         const uint32_t cur = pack4(rt);
         *(uint32_t*)(st + so.k + (size_t)chain * Npad + n0) = cur;
@@ -1235,10 +1263,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
 // items from the list until it is exhausted, each with its class's arguments (a separate
 // instantiation, so that the direct kernels keep their registers).
 template <typename Real, int RTW, int WD, bool MG, int Q, int PM, bool EVAL, int WIN, int KND, bool CX, bool PERS,
-          bool FULL = false>
+          bool FULL = false, bool HALF = false>
 __device__ __forceinline__ void sampler_entry(const SamplerArgs& a, const Persist& p) {
   if constexpr (!PERS) {
-    sampler_body<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX, FULL>(a, blockIdx.x, blockIdx.y);
+    sampler_body<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX, FULL, HALF>(a, blockIdx.x, blockIdx.y);
   } else {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     for (;;) {
@@ -1246,17 +1274,17 @@ __device__ __forceinline__ void sampler_entry(const SamplerArgs& a, const Persis
       if (it >= p.n_items) break;
       const WorkItem w = p.items[it];
       const SamplerArgs ca = ((const SamplerArgs*)p.cls)[__builtin_amdgcn_readfirstlane(w.cls)];
-      sampler_body<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX>(ca, __builtin_amdgcn_readfirstlane(w.inst),
-                                                                 __builtin_amdgcn_readfirstlane(w.cg));
+      sampler_body<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX, false, HALF>(
+          ca, __builtin_amdgcn_readfirstlane(w.inst), __builtin_amdgcn_readfirstlane(w.cg));
     }
     persist_done(p);
   }
 }
 
 template <typename Real, int RTW, int WD, bool MG, int Q, int PM, bool EVAL, int WIN, int KND, bool CX = false,
-          bool PERS = false>
+          bool PERS = false, bool HALF = false>
 __global__ __launch_bounds__(256) void sampler_kernel(SamplerArgs a, Persist p) {
-  sampler_entry<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX, PERS>(a, p);
+  sampler_entry<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX, PERS, false, HALF>(a, p);
 }
 
 // The same kernel held to two waves per SIMD (at most 256 registers): the
@@ -1340,7 +1368,13 @@ hipError_t launch_t(const Shape& sh, const SamplerArgs& a, bool eval, hipStream_
   constexpr bool kFull = KND == 0 && CX && !std::is_same<Real, double>::value;
   const bool full = sh.N == sh.Npad;
   const bool pers = (p != nullptr || cfg != nullptr) && !eval;
-  if (pers) {
+  // up to 8 antennas: the 32-dimension layout without its padding tile (half the work per chain)
+  constexpr bool kHalf = KND == 0 && RTW == 2 && WD == 1 && !std::is_same<Real, double>::value;
+  const bool half = kHalf && sh.N <= 16;
+  if (half && !eval) {
+    if constexpr (kHalf) k = pers ? sampler_kernel<Real, RTW, WD, MG, Q, PM, false, WIN, KND, CX, true, true>
+                                  : sampler_kernel<Real, RTW, WD, MG, Q, PM, false, WIN, KND, CX, false, true>;
+  } else if (pers) {
     if constexpr (kPersOK) {
       if (waves > 4) {
         if constexpr (kW2 && WD == 4) k = sampler_kernel_w2_512<Real, RTW, WD, MG, Q, PM, false, WIN, KND, CX, true>;

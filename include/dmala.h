@@ -122,7 +122,9 @@ typedef struct {
   double beta_mult;          /* beta  = beta_mult * dmin^2 / sigma^2;  <= 0 selects 1 */
   double gamma_mult;         /* gamma = gamma_mult * sigma^2 / (2 dmin^2); <= 0 selects 1 */
   int32_t tile_config;       /* sampler work layout: 0 = automatic (32 dims: layout 0, 64: 9, 128: 7,
-                                256: 8 (NAIVE: 1, 3, 4); LEARNED 64: 5, 128: 6); k >= 1 selects layout k - 1:
+                                256: 8 (NAIVE: 1, 3, 4); LEARNED 64: 5, 128: 6; PRECOND launches that would
+                                leave most of the GPU idle run layouts 0, 9 and 7 with each chain block
+                                spread over more waves, with the same results bit for bit); k >= 1 selects layout k - 1:
                                 0: 32 dims, 1 wave / 16 chains, matrices in LDS
                                 1: 64 dims, 1 wave / 16 chains, LDS
                                 2: 128 dims, 1 wave / 16 chains, LDS

@@ -108,6 +108,7 @@ dmala_status make_plan(int32_t n_inst, int32_t nt, int32_t nr, int32_t M, const 
   set_frag_bytes();
   if (sampler_lds_bytes(sh) > 160 * 1024)
     return fail(DMALA_ERR_UNSUPPORTED, "shape needs %zu bytes of LDS (> 160 KiB)", sampler_lds_bytes(sh));
+  sh.spread = p->tile_config == 0 && p->wg_chain_blocks == 0 && sampler_load(sh, n_inst) <= 1.0 ? 1 : 0;
   sh.inst_bytes = round_up(kParamBytes + sh.frag_bytes, 256);
   sh.state_bytes = state_offsets(sh.Cpad, sh.Npad).end;
   sh.wscratch_bytes = setup_w_global(nt) ? round_up((size_t)nt * (nt + 1) * 16, 256) : 0;

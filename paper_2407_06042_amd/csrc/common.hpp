@@ -69,6 +69,7 @@ struct Shape {
   int share;       // 1: launched beside other classes' kernels (an uneven batch's graph branches)
   int mhgd;        // 1: the MHGD baseline kernel (nearest-point candidate, MH without the proposal ratio)
   int cx;          // 1: matrices packed as complex planes (layouts 7, 8)
+  int spread;      // 1: the layout's chain blocks spread over more waves (sampler_spread.hpp)
   size_t inst_bytes;   // per-instance setup block
   size_t frag_bytes;   // MFMA fragments (MFMA path)
   size_t state_bytes;  // per-instance sampler->estimator block
@@ -225,6 +226,7 @@ hipError_t launch_estimate(const EstArgs& a, hipStream_t s, const Persist* p = n
 size_t sampler_lds_bytes(const Shape& sh);
 bool sampler_cfg_valid(const Shape& sh, int cfg);
 int sampler_default_cfg(const Shape& sh);
+double sampler_load(const Shape& sh, int n_inst);
 int estimate_chunk(int nt, int nr, int M, int N, int C, bool fp64);
 
 // ------------------------------------------------------------------ device helpers
@@ -239,21 +241,26 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t k) {
 // by the Weyl constants between rounds.  BITOP3: the xors as three-input bit
 // operations.
 template <bool BITOP3>
+__device__ __forceinline__ void philox4x32_round(uint32_t c[4], uint32_t k0, uint32_t k1) {
+  const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
+  const uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
+  uint32_t n0, n2;
+  if constexpr (BITOP3) {
+    n0 = xor3((uint32_t)(p1 >> 32), c[1], k0);
+    n2 = xor3((uint32_t)(p0 >> 32), c[3], k1);
+  } else {
+    n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0;
+    n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
+  }
+  c[0] = n0; c[1] = (uint32_t)p1; c[2] = n2; c[3] = (uint32_t)p0;
+}
+
+template <bool BITOP3>
 __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-    const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
-    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
-    uint32_t n0, n2;
-    if constexpr (BITOP3) {
-      n0 = xor3((uint32_t)(p1 >> 32), c[1], k0);
-      n2 = xor3((uint32_t)(p0 >> 32), c[3], k1);
-    } else {
-      n0 = (uint32_t)(p1 >> 32) ^ c[1] ^ k0;
-      n2 = (uint32_t)(p0 >> 32) ^ c[3] ^ k1;
-    }
-    c[0] = n0; c[1] = (uint32_t)p1; c[2] = n2; c[3] = (uint32_t)p0;
+    philox4x32_round<BITOP3>(c, k0, k1);
   }
 }
 

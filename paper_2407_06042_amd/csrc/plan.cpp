@@ -76,6 +76,7 @@ struct dmala_plan_s {
   InstDesc* desc_dev = nullptr;
   size_t ws_total = 0;
   int n_branches = 1;
+  bool spread = false;      // the whole plan is small enough for the spread sampler kernels (sampler_load)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   std::vector<const void*> key;
@@ -113,6 +114,8 @@ dmala_status class_plan(dmala_plan_s* P, ClassInfo& c) {
   p.wg_chain_blocks = c.cbw;
   const dmala_status st = make_plan(c.count, c.shape.nt, c.shape.nr, c.shape.qam_order, &p, c.pl);
   c.pl.sh.share = 1;
+  // (the classes share the GPU: spread over more waves when all of them together leave it room)
+  if (!P->spread) c.pl.sh.spread = 0;
   return st;
 }
 
@@ -465,6 +468,12 @@ dmala_status dmala_plan_create(dmala_plan* plan, const dmala_shape* shapes, int3
       return st;
     }
     P->classes.push_back(c);
+  }
+  double load = 0.0;
+  for (auto& c : P->classes) load += sampler_load(c.pl.sh, c.count);
+  if (load <= 1.0) {
+    P->spread = true;
+    for (auto& c : P->classes) (void)class_plan(P, c);
   }
   std::sort(P->classes.begin(), P->classes.end(), [](const ClassInfo& a, const ClassInfo& b) { return a.cost > b.cost; });
   std::vector<InstDesc> table;

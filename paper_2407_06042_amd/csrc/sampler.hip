@@ -17,6 +17,9 @@ hipError_t launch_sampler_lrn_bf16x1(const Shape&, const SamplerArgs&, bool, hip
 hipError_t launch_sampler_mhgd_f64(const Shape&, const SamplerArgs&, bool, hipStream_t, const Persist*, int, KernelCfg*);
 hipError_t launch_sampler_mhgd_f16x2(const Shape&, const SamplerArgs&, bool, hipStream_t, const Persist*, int, KernelCfg*);
 hipError_t launch_sampler_mhgd_bf16x1(const Shape&, const SamplerArgs&, bool, hipStream_t, const Persist*, int, KernelCfg*);
+hipError_t launch_spread_f16x2(const Shape&, const SamplerArgs&, hipStream_t, const Persist*, int, KernelCfg*);
+hipError_t launch_spread_f16x1(const Shape&, const SamplerArgs&, hipStream_t, const Persist*, int, KernelCfg*);
+hipError_t launch_spread_bf16x1(const Shape&, const SamplerArgs&, hipStream_t, const Persist*, int, KernelCfg*);
 
 size_t sampler_lds_bytes(const Shape& sh) {
   if (sh.fp64) {
@@ -65,6 +68,31 @@ int sampler_default_cfg(const Shape& sh) {
   return -1;
 }
 
+// How much of the GPU n_inst instances keep busy with their chain blocks spread over more waves
+// (sampler_spread.hpp): at most 1 where that form is the faster one.  Measured with 64-QAM, 32 chains x 100
+// transitions, fp32, spread against the layout's own kernel: 32 dimensions (2 waves per block instead of 1)
+// 116 against 188 us for one problem, 155/247 at 1024 blocks, 294/263 at 2048; 64 dimensions (4 instead of 1)
+// 134/350, 329/475 at 1024, 632/518 at 2048; 128 dimensions (8 instead of 2) 210/441, 231/450 at 256 (a
+// workgroup takes a CU's registers), 436/453 at 384, 850/604 at 1024.  Launches that cannot be spread
+// (256 dimensions: their matrices do not fit the registers; up to 16 real dimensions: one wave per block has
+// no more than four per lane) count by their own waves, and infinite where the form does not exist.
+double sampler_load(const Shape& sh, int n_inst) {
+  const double blocks = (double)n_inst * (sh.Cpad / 16);
+  if (sh.fp64 || sh.lrn || sh.mhgd || sh.pm == PM_NAIVE) return 1e30;
+  switch (sh.cfg) {
+    case 0: return blocks / (sh.N <= 16 ? 4096.0 : 1536.0);
+    case 9: return blocks / 1024.0;
+    case 7: return blocks / 256.0;
+    case 8: return blocks / 256.0;
+  }
+  return 1e30;
+}
+
+// Whether a shape's chain blocks can be spread (the preconditioned float chains in the layouts above).
+static bool spreadable(const Shape& sh) {
+  return !sh.fp64 && !sh.lrn && !sh.mhgd && sh.pm != PM_NAIVE && (sh.cfg == 9 || sh.cfg == 7 || (sh.cfg == 0 && sh.N > 16));
+}
+
 hipError_t launch_sampler(const Shape& sh, const SamplerArgs& a, bool eval, hipStream_t s, const Persist* p, int gn,
                     KernelCfg* cfg) {
   if (sh.mhgd) {
@@ -79,6 +107,14 @@ hipError_t launch_sampler(const Shape& sh, const SamplerArgs& a, bool eval, hipS
       case PM_F16X2: return launch_sampler_lrn_f16x2(sh, a, eval, s, p, gn, cfg);
       case PM_F16X1: return launch_sampler_lrn_f16x1(sh, a, eval, s, p, gn, cfg);
       case PM_BF16X1: return launch_sampler_lrn_bf16x1(sh, a, eval, s, p, gn, cfg);
+    }
+    return hipErrorInvalidValue;
+  }
+  if (sh.spread && spreadable(sh) && !eval) {
+    switch (sh.pm) {
+      case PM_F16X2: return launch_spread_f16x2(sh, a, s, p, gn, cfg);
+      case PM_F16X1: return launch_spread_f16x1(sh, a, s, p, gn, cfg);
+      case PM_BF16X1: return launch_spread_bf16x1(sh, a, s, p, gn, cfg);
     }
     return hipErrorInvalidValue;
   }

@@ -244,7 +244,7 @@ __device__ __forceinline__ R log2_norm(R mu, R kL, const WinCoef& wc) {
 // Inverse-CDF draw: the smallest level j with u Z < sum_{i <= j} w_i
 // (ascending levels), Z = sum_i w_i; the level as a floating-point integer.
 template <int Q, int WIN, int W, bool TAB, typename R>
-__device__ __forceinline__ R draw_level(R mu, R kL, const WinCoef& wc, uint32_t word) {
+__device__ __forceinline__ R draw_level(R mu, R kL, const WinCoef& wc, uint32_t word, float kB) {
   if constexpr (WIN > 0) {
     R e[2 * W + 1];
     R jf, delta;
@@ -255,8 +255,8 @@ __device__ __forceinline__ R draw_level(R mu, R kL, const WinCoef& wc, uint32_t 
     // The partial sums above the target, counted in fp32 without compares: with B = 2^100,
     // B (cum - target) is exact in sign and, since target >= 2^-24 Z and cum, target are
     // fp32 numbers, at least B 2^-47 when positive; clamped to [0, 1] it is the 0/1
-    // indicator of cum > target (one fused multiply-add with the clamp modifier each).
-    constexpr float kB = 0x1p100f;
+    // indicator of cum > target (one fused multiply-add with the clamp modifier each).  B comes in a
+    // vector register: with a scalar operand each would issue at half the rate.
     const R tB = u23f_x2p100(word) * Z;   // (u Z) 2^100, rounded once as u Z
     R cum = e[0];
     R above = __builtin_amdgcn_fmed3f(0.0f, 1.0f, __builtin_fmaf(cum, kB, -tB));
@@ -527,6 +527,28 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
     return v;
   };
 
+  // Complex planes from L2: the energy planes of an antenna tile that are not in LDS, loaded ahead of their
+  // products (the first tile's before the draw, whose registers the proposal's centres take up only
+  // after it; the next tile's before the products of the one before).  128 dimensions, fp32: 6 loads of the
+  // tile's 20, 24 registers; 64x64 64-QAM sampler 8.87 -> 8.64 ms together with the accepting branch below.
+  // At 256 dimensions the 28 loads of a tile do not fit the registers.
+  constexpr int KBP = CX ? RT / 4 : 1;
+  // half passes of the energy matrix from L2: in storage order after the NPP proposal passes
+  constexpr int kAhead = CX && MG ? 2 * kEPasses - (SPH > 2 * NPP ? (SPH - 2 * NPP < 2 * kEPasses ? SPH - 2 * NPP : 2 * kEPasses) : 0) : 0;
+  constexpr bool AHEAD = KND == 0 && !EVAL && kAhead > 0 && kAhead * KBP <= 8;
+  struct Ahead { uint4 v[AHEAD ? kAhead * KBP : 1]; };
+  auto load_ahead = [&](int at, Ahead& o) {
+    if constexpr (AHEAD) {
+      const unsigned char* src = blk + kParamBytes + opaque_zero() + (uint32_t)lane * 16;
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+        for (int kb = 0; kb < KBP; ++kb)
+          o.v[i * KBP + kb] = *(const uint4*)(src + (uint32_t)(((2 * (NPP + kEPasses) - kAhead + i) * (RT / 2) + (rt0 >> 1) + at) * KBP + kb) * 1024u);
+    }
+  };
+  Ahead ahead;
+
   // [P; EG] x lv(k): accP/accE hold the lane's D outputs.  hook(rt) runs after the
   // products of row tile rt are issued (independent work placed there overlaps them).
   auto contract = [&](const Real (&k)[D], Real (&accP)[D], Real (&accE)[D], auto&& hook) {
@@ -639,7 +661,12 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
 #pragma unroll
           for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
-            for (int kb = 0; kb < KBX; ++kb) fe[p][pl][kb] = *(const uint4*)frag(NPP + p, pl, atg, kb);
+            for (int kb = 0; kb < KBX; ++kb) {
+              constexpr int first = 2 * kEPasses - kAhead;
+              if (AHEAD && 2 * p + pl >= first) fe[p][pl][kb] = ahead.v[(2 * p + pl - first) * KBX + kb];
+              else fe[p][pl][kb] = *(const uint4*)frag(NPP + p, pl, atg, kb);
+            }
+        if (at + 1 < ATW) load_ahead(at + 1, ahead);
         f32x4 er = {0.f, 0.f, 0.f, 0.f}, ei = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int p = 0; p < kEPasses; ++p)
@@ -1013,8 +1040,11 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         norm_parts<Q, WIN, W, TAB>(Real((int)(((uint64_t)(c[i] >> 8) * Q) >> 24)), kL, wc, zpad[i], b2);
       }
     }
+    float kB = 0x1p100f;   // the draw's indicator scale
+    asm volatile("" : "+v"(kB));
     Real muL[D], kLL[D];  // cached learned proposal (LRN)
     Real lzs = 0;         // sum of the lane's log2 normalisers at the current state (plain kernel)
+    load_ahead(0, ahead);
     if constexpr (LRN) {
       grad_at(kc, mu, eg, nohook);
       learned_at(kc, mu, muL, kLL);
@@ -1074,6 +1104,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       for (int rt = 0; rt < RTA; ++rt) word_block(rt, 1);
     }
     for (int t = 1; t <= a.T; ++t) {
+      load_ahead(0, ahead);
       if constexpr (!PIPE) {
 #pragma unroll
         for (int rt = 0; rt < RTA; ++rt) word_block(rt, t);
@@ -1105,7 +1136,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           const float t0 = float(kp[d]) - ms;
           S -= valid[d] ? (-ks * t0 * t0 - lzf) : 0.f;
         } else {
-          const Real kd = draw_level<Q, WIN, W, TAB>(mu[d], kL, wc, w[d >> 2][d & 3]);
+          const Real kd = draw_level<Q, WIN, W, TAB>(mu[d], kL, wc, w[d >> 2][d & 3], kB);
           kp[d] = valid[d] ? kd : kc[d];
           const Real t0 = Real(kp[d]) - mu[d];
           tq += t0 * t0;
@@ -1181,24 +1212,39 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         T2 = bfly4(T2);
       }
       const bool acc = S > Real(0);
-      // 5. select
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        kc[d] = acc ? kp[d] : kc[d];
-        mu[d] = acc ? mup[d] : mu[d];
-        eg[d] = acc ? egp[d] : eg[d];
-        if constexpr (LRN) {
-          muL[d] = acc ? muLp[d] : muL[d];
-          kLL[d] = acc ? kLLp[d] : kLL[d];
-        }
-      }
-      if constexpr (KND == 0) lzs = acc ? lzps : lzs;
-      E = acc ? E - T2 * eunit : E;
-      nacc += acc ? 1 : 0;
-      if (E < Ebest) {
+      // 5. accepted chains take over the proposal's values
+      auto best = [&]() {
         Ebest = E;
 #pragma unroll
         for (int rt = 0; rt < RTA; ++rt) kbest[rt] = pack4(rt);
+      };
+      if constexpr (LRN) {
+        // (selects: with the network's registers the branch below measured 2 % slower)
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          kc[d] = acc ? kp[d] : kc[d];
+          mu[d] = acc ? mup[d] : mu[d];
+          eg[d] = acc ? egp[d] : eg[d];
+          muL[d] = acc ? muLp[d] : muL[d];
+          kLL[d] = acc ? kLLp[d] : kLL[d];
+        }
+        E = acc ? E - T2 * eunit : E;
+        nacc += acc ? 1 : 0;
+        if (E < Ebest) best();
+      } else if (acc) {
+        // moves under the lanes' mask, skipped when every chain of the wave rejects, as in about half of
+        // all transitions (the empty asm keeps the branch)
+        asm volatile("");
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          kc[d] = kp[d];
+          mu[d] = mup[d];
+          eg[d] = egp[d];
+        }
+        if constexpr (KND == 0) lzs = lzps;
+        E = E - T2 * eunit;
+        nacc += 1;
+        if (E < Ebest) best();
       }
       if (a.trace_accept) {
         abits |= (acc ? 1u : 0u) << ((t - 1) & 31);

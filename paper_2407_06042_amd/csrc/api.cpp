@@ -121,6 +121,7 @@ dmala_status make_plan(int32_t n_inst, int32_t nt, int32_t nr, int32_t M, const 
   pl.bm = p->beta_mult > 0 ? p->beta_mult : 1.0;
   pl.gm = p->gamma_mult > 0 ? p->gamma_mult : 1.0;
   pl.mix_thr = 0;
+  pl.n_beside = 0;
   if (lrn) {
     const double t = std::ceil(p->mix_eps * 16777216.0);
     pl.mix_thr = (uint32_t)(t < 0 ? 0 : (t > 16777216.0 ? 16777216.0 : t));
@@ -184,7 +185,7 @@ void make_args(const void* H, const void* y, const void* sigma2, int32_t n_inst,
   ea.ws_state = base + pl.state_off; ea.state_stride = sh.state_bytes;
   ea.n_inst = n_inst; ea.nt = sh.nt; ea.nr = sh.nr; ea.Q = sh.Q; ea.N = sh.N; ea.Npad = sh.Npad;
   ea.C = sh.C; ea.Cpad = sh.Cpad; ea.fp64 = sh.fp64;
-  ea.chunk = estimate_chunk(sh.nt, sh.nr, sh.M, sh.N, sh.C, sh.fp64 != 0);
+  estimate_shape(&ea, sh.nt, sh.nr, sh.M, sh.N, sh.C, sh.fp64 != 0, pl.n_beside > n_inst ? pl.n_beside : n_inst);
   ea.llr_mode = (int)p->llr_mode;
   ea.llr_clip = 20.0f;
   if (out) {

@@ -160,6 +160,9 @@ struct EstArgs {
   const unsigned char* ws_state; size_t state_stride;
   int n_inst, nt, nr, Q, N, Npad, C, Cpad, fp64;
   int chunk;       // chains staged in LDS at a time
+  int threads;     // per workgroup: 256, 512 or 1024
+  int res;         // order of the residual sums (0 to 2, see the kernel)
+  int gm, gl;      // threads that share a marginal row's and a bit's chains
   int32_t* symbols; float* marginals; float* llrs; float* best_energy; float* marginals_mc;
   int llr_mode;    // 0: IS (eq. llr_is), 1: list (eq. llr_approx_app), 2: Monte Carlo bit frequencies (eq. mc)
   float llr_clip;  // |LLR| limit of the list and Monte Carlo forms
@@ -227,7 +230,8 @@ size_t sampler_lds_bytes(const Shape& sh);
 bool sampler_cfg_valid(const Shape& sh, int cfg);
 int sampler_default_cfg(const Shape& sh);
 double sampler_load(const Shape& sh, int n_inst);
-int estimate_chunk(int nt, int nr, int M, int N, int C, bool fp64);
+// Threads, chunk, sums' order and groups for a shape with C chains in a launch of n_inst instances.
+void estimate_shape(EstArgs* ea, int nt, int nr, int M, int N, int C, bool fp64, int n_inst);
 
 // ------------------------------------------------------------------ device helpers
 

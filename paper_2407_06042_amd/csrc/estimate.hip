@@ -45,8 +45,6 @@ struct OnlineLse {
 };
 
 constexpr int kLlrPerThread = 4;  // bits per instance <= 128 antennas x 8 bits = 4 x 256 threads
-// Workgroups of 1024 threads serve instances with more than 256 (antenna, kI) rows: fewer row
-// blocks, so the chain chunks are staged (residuals, H^H r) fewer times, and 16 waves per CU.
 
 // Exchanges inside groups of Q consecutive lanes (Q <= 16, so a group never straddles a 32-lane
 // half) by ds_swizzle in its bit mode: lane j reads lane ((j & and) | or) ^ xor of its half, an
@@ -77,8 +75,10 @@ struct CM {
   int kI, kQ;
 };
 
-template <typename R, int Q, bool SH, int BS>
-__device__ __forceinline__ void estimate_body(const EstArgs& a, const int b) {
+// The float64 path (at most 32 antennas, 256 threads).
+template <int Q, bool SH>
+__device__ __forceinline__ void estimate_d(const EstArgs& a, const int b) {
+  using R = double;
   constexpr int M = Q * Q;
   constexpr int NB = Q == 2 ? 1 : (Q == 4 ? 2 : (Q == 8 ? 3 : 4));
   const int tid = threadIdx.x, nth = blockDim.x;
@@ -105,7 +105,6 @@ __device__ __forceinline__ void estimate_body(const EstArgs& a, const int b) {
   const R s = (R)ip.s, tau = (R)ip.tau;
   const R inv_s2 = R(1) / (R)ip.sigma2, inv_tau = R(1) / tau;
   const R cw = (tau - R(1)) * inv_tau;
-  const R kA = R(-2) * tau * R(0.69314718055994530942);
   const StateOff so = state_offsets(a.Cpad, Npad);
   const unsigned char* st = a.ws_state + (size_t)b * a.state_stride;
   const int8_t* K = (const int8_t*)(st + so.k);
@@ -217,136 +216,6 @@ __device__ __forceinline__ void estimate_body(const EstArgs& a, const int b) {
         }
         __syncthreads();
         // residuals of the final and of the best states
-        if constexpr (std::is_same<R, float>::value && BS >= 512) {
-          // (the 256-thread workgroups, held to 96 registers, keep the loop below)
-          // On the float32 matrix cores (v_mfma_f32_16x16x4f32: float32 H times the integer
-          // level indices): [Re r; Im r] = y' - 2 s [Hr -Hi; Hi Hr] k over the real dimensions
-          // n = 2m (kI of antenna m), 2m + 1 (kQ), so that B[n][c] is the staged level byte of
-          // chain c.  A unit is one 16-row tile of receive antennas (its real and imaginary rows)
-          // and one 16-chain tile, for the final and the best states together; lane l holds
-          // A[l % 16][4 s + l / 16], B[4 s + l / 16][l % 16] and the outputs at rows 4 (l / 16) + j.
-          typedef float f32x4 __attribute__((ext_vector_type(4)));
-          // With at least twice as many waves as units (1024-thread workgroups), every unit's K
-          // steps are split between two waves (otherwise half the waves would idle): the second
-          // half's accumulators go through the per-(chain, antenna) array, unused until the
-          // normalisers below, and are added to the first half's in a fixed order.  (In the
-          // 512-thread workgroups the split form's registers would cost the second workgroup per CU.)
-          bool ksplit = false;
-          if constexpr (BS >= 1024) {
-            const int lane = tid & 63, wv = tid >> 6, nwv = nth >> 6;
-            const int nrt = (nr + 15) >> 4, nct = (ch + 15) >> 4, ksteps = (N + 3) >> 2, units = nrt * nct;
-            ksplit = 2 * units <= nwv && (size_t)units * 64 * 16 * sizeof(float) <= (size_t)ch * nt * sizeof(CM<R>);
-            if (ksplit) {
-              constexpr int kU = 2;
-              const int uu = wv % units, kh = wv / units;   // one item per wave
-              const int half = ((ksteps + 1) / 2 + kU - 1) / kU * kU;
-              const int st_a = kh ? half : 0, st_b = kh ? ksteps : half;
-              const int rt = uu % nrt, ct = uu / nrt;
-              const int ia = 16 * rt + (lane & 15), c = 16 * ct + (lane & 15);
-              const int iac = ia < nr ? ia : nr - 1, cc = c < ch ? c : ch - 1;
-              f32x4 fre = {0.f, 0.f, 0.f, 0.f}, fim = fre, bre = fre, bim = fre;
-              for (int st0 = st_a; kh < 2 && st0 < st_b; st0 += kU) {
-                R hr0[kU], hi0[kU];
-                uint8_t kf0[kU], kb0[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                  const int n = 4 * (st0 + u) + (lane >> 4), nc = n < N ? n : N - 1, m = nc >> 1;
-                  hr0[u] = hre(m, iac);
-                  hi0[u] = him(m, iac);
-                  kf0[u] = (uint8_t)Ks[cc * N + nc];
-                  kb0[u] = (uint8_t)Kbs[cc * N + nc];
-                }
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                  // steps past N or past this half's end: zero
-                  const int n = 4 * (st0 + u) + (lane >> 4);
-                  const bool kin = n < N && st0 + u < st_b;
-                  const bool aok = kin && ia < nr, bok = kin && c < ch;
-                  const R hr = aok ? hr0[u] : R(0), hi = aok ? hi0[u] : R(0);
-                  const R are = (n & 1) ? -hi : hr, aim = (n & 1) ? hr : hi;
-                  const R kf = bok ? R(kf0[u]) : R(0), kb = bok ? R(kb0[u]) : R(0);
-                  fre = __builtin_amdgcn_mfma_f32_16x16x4f32(are, kf, fre, 0, 0, 0);
-                  fim = __builtin_amdgcn_mfma_f32_16x16x4f32(aim, kf, fim, 0, 0, 0);
-                  bre = __builtin_amdgcn_mfma_f32_16x16x4f32(are, kb, bre, 0, 0, 0);
-                  bim = __builtin_amdgcn_mfma_f32_16x16x4f32(aim, kb, bim, 0, 0, 0);
-                }
-              }
-              float* part = (float*)cm + (size_t)uu * 64 * 16;
-              if (kh == 1) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                  part[(0 + j) * 64 + lane] = fre[j];
-                  part[(4 + j) * 64 + lane] = fim[j];
-                  part[(8 + j) * 64 + lane] = bre[j];
-                  part[(12 + j) * 64 + lane] = bim[j];
-                }
-              }
-              __syncthreads();
-              if (kh == 0) {
-                const R s2 = R(2) * s;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                  const int i = 16 * rt + 4 * (lane >> 4) + j;
-                  const float pre = fre[j] + part[(0 + j) * 64 + lane], pim = fim[j] + part[(4 + j) * 64 + lane];
-                  const float pbr = bre[j] + part[(8 + j) * 64 + lane], pbi = bim[j] + part[(12 + j) * 64 + lane];
-                  if (i < nr && c < ch) {
-                    rs[c * lrs + 2 * i] = ys[2 * i] - s2 * pre;
-                    rs[c * lrs + 2 * i + 1] = ys[2 * i + 1] - s2 * pim;
-                    const R br = ys[2 * i] - s2 * pbr, bi = ys[2 * i + 1] - s2 * pbi;
-                    rb2[c * nr + i] = br * br + bi * bi;
-                  }
-                }
-              }
-            }
-          }
-          if (!ksplit) {
-            const int lane = tid & 63, nrt = (nr + 15) >> 4, nct = (ch + 15) >> 4, ksteps = (N + 3) >> 2;
-            const R s2 = R(2) * s;
-            for (int u = tid >> 6; u < nrt * nct; u += nth >> 6) {
-              const int rt = u % nrt, ct = u / nrt;
-              const int ia = 16 * rt + (lane & 15), c = 16 * ct + (lane & 15);
-              // every load in bounds (indices clamped, values masked after), so that none is predicated
-              const int iac = ia < nr ? ia : nr - 1, cc = c < ch ? c : ch - 1;
-              f32x4 fre = {0.f, 0.f, 0.f, 0.f}, fim = fre, bre = fre, bim = fre;
-              // two K steps per pass: all their loads issue before the first product
-              constexpr int kU = 2;
-              for (int st0 = 0; st0 < ksteps; st0 += kU) {
-                R hr0[kU], hi0[kU];
-                uint8_t kf0[kU], kb0[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                  const int n = 4 * (st0 + u) + (lane >> 4), nc = n < N ? n : N - 1, m = nc >> 1;
-                  hr0[u] = hre(m, iac);
-                  hi0[u] = him(m, iac);
-                  kf0[u] = (uint8_t)Ks[cc * N + nc];
-                  kb0[u] = (uint8_t)Kbs[cc * N + nc];
-                }
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                  const int n = 4 * (st0 + u) + (lane >> 4);   // n >= N (K padding, steps past the end): zero
-                  const bool aok = n < N && ia < nr, bok = n < N && c < ch;
-                  const R hr = aok ? hr0[u] : R(0), hi = aok ? hi0[u] : R(0);
-                  const R are = (n & 1) ? -hi : hr, aim = (n & 1) ? hr : hi;
-                  const R kf = bok ? R(kf0[u]) : R(0), kb = bok ? R(kb0[u]) : R(0);
-                  fre = __builtin_amdgcn_mfma_f32_16x16x4f32(are, kf, fre, 0, 0, 0);
-                  fim = __builtin_amdgcn_mfma_f32_16x16x4f32(aim, kf, fim, 0, 0, 0);
-                  bre = __builtin_amdgcn_mfma_f32_16x16x4f32(are, kb, bre, 0, 0, 0);
-                  bim = __builtin_amdgcn_mfma_f32_16x16x4f32(aim, kb, bim, 0, 0, 0);
-                }
-              }
-#pragma unroll
-              for (int j = 0; j < 4; ++j) {
-                const int i = 16 * rt + 4 * (lane >> 4) + j;
-                if (i < nr && c < ch) {
-                  rs[c * lrs + 2 * i] = ys[2 * i] - s2 * fre[j];
-                  rs[c * lrs + 2 * i + 1] = ys[2 * i + 1] - s2 * fim[j];
-                  const R br = ys[2 * i] - s2 * bre[j], bi = ys[2 * i + 1] - s2 * bim[j];
-                  rb2[c * nr + i] = br * br + bi * bi;
-                }
-              }
-            }
-          }
-        } else
         for (int it = tid; it < ch * nr; it += nth) {
           const int c = it / nr, i = it % nr;
           const uint16_t* kf = (const uint16_t*)(Ks + c * N);   // (k_I, k_Q) of antenna m, as bytes
@@ -388,14 +257,7 @@ __device__ __forceinline__ void estimate_body(const EstArgs& a, const int b) {
         for (int it = tid; it < ch * nt; it += nth) {
           const int c = SH ? it / nt : it % ch, m = SH ? it % nt : it / ch;
           CM<R> v;
-          if constexpr (std::is_same<R, float>::value) {
-            // from the sampler's energy gradient at the final state,
-            // g = 2 s log2(e) (G x - z) / (tau sigma^2) = -2 s log2(e) H^H r / (tau sigma^2):
-            // 4 s (H^H r) / sigma^2 = -2 tau ln(2) g
-            const float* egc = (const float*)(st + so.eg) + (size_t)(c0 + c) * Npad;
-            v.aI = kA * egc[2 * m];
-            v.aQ = kA * egc[2 * m + 1];
-          } else {
+          {
             R re = 0, im = 0;
             for (int i = 0; i < nr; ++i) {
               const R hr = hre(m, i), hi = him(m, i);
@@ -408,25 +270,7 @@ __device__ __forceinline__ void estimate_body(const EstArgs& a, const int b) {
           }
           v.kI = Ks[c * N + 2 * m];
           v.kQ = Ks[c * N + 2 * m + 1];
-          if constexpr (std::is_same<R, float>::value) {
-            // per-axis log normalisers over the Q levels, accumulated in log2 units (no scaling
-            // before each exponential); the level offsets are exact float differences
-            const R sc = inv_tau * R(1.4426950408889634);
-            const R q2s = a2[m] * sc, aIs = v.aI * sc, aQs = v.aQ * sc;
-            const R kIf = R(v.kI), kQf = R(v.kQ);
-            R mi = R(-INFINITY), mq = R(-INFINITY), si = R(0), sq = R(0);
-#pragma unroll
-            for (int k = 0; k < Q; ++k) {
-              const R eI = R(k) - kIf, eQ = R(k) - kQf;
-              const R ti = eI * (aIs - q2s * eI), tq = eQ * (aQs - q2s * eQ);
-              const R ni = fmax(mi, ti), nq = fmax(mq, tq);
-              si = si * fex2(mi - ni) + fex2(ti - ni);
-              sq = sq * fex2(mq - nq) + fex2(tq - nq);
-              mi = ni;
-              mq = nq;
-            }
-            v.base = cw * fs[c] - (mi + flg2(si) + mq + flg2(sq)) * R(0.6931471805599453);
-          } else {
+          {
             const R q2 = a2[m];
             OnlineLse<R> li, lq;
 #pragma unroll
@@ -591,13 +435,580 @@ __device__ __forceinline__ void estimate_body(const EstArgs& a, const int b) {
   }
 }
 
+
+// A sum of exponentials 2^(v - mx) with its running maximum mx, values in log2 units: one exponential per
+// value (of the distance to the maximum) instead of one for the old sum and one for the value.
+struct Lse2 {
+  float mx = -INFINITY, sum = 0.f;
+  __device__ __forceinline__ void add(float v) {
+    const float d = v - mx, e = fex2(-fabsf(d));
+    sum = d > 0.f ? __builtin_fmaf(sum, e, 1.f) : sum + e;
+    mx = fmaxf(v, mx);
+  }
+  // merge another sum (either may be empty)
+  __device__ __forceinline__ void add(float omx, float osum) {
+    if (omx == -INFINITY) return;
+    const float m2 = fmaxf(mx, omx);
+    sum = sum * fex2(mx - m2) + osum * fex2(omx - m2);
+    mx = m2;
+  }
+  __device__ __forceinline__ float value() const { return (mx + flg2(sum)) * 0.6931471805599453f; }
+};
+
+// Threads that share a row's (or a bit's) chains: the largest power of two that keeps them within the given threads,
+// at most 8.
+__host__ __device__ inline int est_groups(int items, int threads) {
+  int g = 1;
+  while (2 * g * items <= threads && g < 8) g *= 2;
+  return g;
+}
+
+// LDS of the float path (bytes): per-(chain, antenna) values -- the residuals before them, the bits' merges after --,
+// energies, per-antenna constants, y', level bytes (rows padded to 16), H.
+struct EstLds {
+  size_t fs, a2, ys, ks, ht, end;
+};
+__host__ __device__ inline EstLds est_lds(int nt, int nr, int Q, int N, int chunk, int gm, int gl, bool h_lds) {
+  const int NB = Q == 2 ? 1 : (Q == 4 ? 2 : (Q == 8 ? 3 : 4)), NS = (N + 15) & ~15;
+  size_t r0 = (size_t)16 * chunk * nt;
+  const size_t res = (size_t)4 * chunk * (3 * (size_t)nr + 2);
+  const size_t mm = (size_t)4 * (2 * Q + 1) * nt * Q * (gm - 1), ml = (size_t)4 * 5 * nt * 2 * NB * (gl - 1);
+  r0 = res > r0 ? res : r0;
+  r0 = mm > r0 ? mm : r0;
+  r0 = ml > r0 ? ml : r0;
+  EstLds o;
+  o.fs = (r0 + 15) & ~(size_t)15;
+  o.a2 = o.fs + (size_t)8 * chunk;
+  o.ys = o.a2 + (size_t)4 * nt;
+  o.ks = (o.ys + (size_t)8 * nr + 15) & ~(size_t)15;
+  o.ht = o.ks + (size_t)2 * chunk * NS;
+  o.end = o.ht + (h_lds ? (size_t)8 * (nt + 1) * nr : 0);
+  return o;
+}
+
+// The float path.  Phases per chunk of chains (one chunk where LDS holds them all): levels staged in LDS;
+// residuals and energies of the final and best states; per (chain, antenna) the axis coefficients and log
+// normalisers; the marginal rows and the bits.
+// |f| reaches 1e5 at high SNR, where one rounding of a quantity of that size moves a marginal by 1e-2: the sums
+// behind f and the marginals keep one order whatever the number of threads (y', the column norms and the energies
+// run sequentially in one thread each, with their loads ahead of the sums; residuals in the form a.res names).
+// Residuals r = y' - 2 s H k from the level indices, y' = y + s (Q - 1) (1 + j) sum_m h_m:
+//   res 0: one thread per (receive antenna, chain);
+//   res 1: on the float32 matrix cores (v_mfma_f32_16x16x4f32, [Re r; Im r] = y' - 2 s [Hr -Hi; Hi Hr] k over the real
+//          dimensions n).  A wave takes a tile of 16 receive antennas x 16 chains of the final or of the best states;
+//          lane l holds A[l % 16][4 s + l / 16], so that whether it multiplies a real or an imaginary column
+//          (n odd) is fixed per lane, and one 16-byte read of its chain's levels serves four K steps;
+//   res 2: the same with the two halves of the K steps summed apart and added.
+// H^H r of the final states comes from the sampler's energy gradient.
+// Bound by issue (per 64x64 64-QAM problem of 64 chains about 16k clocks of float32 MFMA, 15k in the rows, 12k in the
+// bits, 8k in the normalisers).  Two-pass normalisers, byte-wise levels, one row per thread whatever the shape and
+// branches inside the bits' chain loop took (us, full batches): 8x8 64-QAM 72 -> 68, 32x32 326 -> 263,
+// 64x64 947 -> 752, 128x128 256-QAM 414 -> 210.
+// RPT: marginal rows per thread (256-QAM beyond 64 antennas has twice as many rows as threads).
+template <int Q, bool SH, int BS, int RPT>
+__device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
+  using R = float;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  constexpr int M = Q * Q, NW = BS / 64;
+  constexpr int NB = Q == 2 ? 1 : (Q == 4 ? 2 : (Q == 8 ? 3 : 4));
+  constexpr float kL2e = 1.4426950408889634f;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nt = a.nt, nr = a.nr, C = a.C, Npad = a.Npad, N = a.N, CH = a.chunk;
+  const InstDesc dsc = inst_desc(a.desc, b, nt, nr, M, C);
+  const float* Hg = (const float*)a.H + 2 * dsc.h_off;
+  const float* y = (const float*)a.y + 2 * dsc.y_off;
+  const InstParams ip = *(const InstParams*)(a.ws_inst + (size_t)b * a.inst_stride);
+  if (ip.nonfinite) {
+    // a flagged instance (see the setup kernel): no samples to estimate from; symbols -1,
+    // every other output NaN (the whole workgroup leaves here)
+    const float nan = __builtin_nanf("");
+    for (int m = tid; m < nt; m += BS)
+      if (a.symbols) a.symbols[dsc.sym_off + m] = -1;
+    for (int e = tid; e < nt * M; e += BS) {
+      if (a.marginals) a.marginals[dsc.marg_off + e] = nan;
+      if (a.marginals_mc) a.marginals_mc[dsc.marg_off + e] = nan;
+    }
+    for (int e = tid; e < nt * 2 * NB; e += BS)
+      if (a.llrs) a.llrs[dsc.llr_off + e] = nan;
+    if (a.best_energy && tid == 0) a.best_energy[dsc.orig] = nan;
+    return;
+  }
+  const R s = (R)ip.s, tau = (R)ip.tau;
+  const R inv_s2 = R(1) / (R)ip.sigma2, inv_tau = R(1) / tau;
+  const R cw = (tau - R(1)) * inv_tau;
+  const R kA = R(-2) * tau * R(0.69314718055994530942);
+  const StateOff so = state_offsets(a.Cpad, Npad);
+  const unsigned char* st = a.ws_state + (size_t)b * a.state_stride;
+  const unsigned char* K = st + so.k;
+  const unsigned char* Kb = st + so.kbest;
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char esm[];
+  const EstLds lo = est_lds(nt, nr, Q, N, CH, a.gm, a.gl, SH);
+  const int NS = (N + 15) & ~15;                 // level row stride (a multiple of 16, at most Npad)
+  const int ldh = nt + 1;                        // H transposed with a padded row: row- and column-wise reads
+  const int lrs = 2 * nr + 2;                    // residual row stride
+  f32x4* cm = (f32x4*)esm;                       // [chain][antenna]: a_I, a_Q, base, packed levels
+  R* rs = (R*)esm;                               // CH x nr complex residuals of the final states
+  R* rb2 = rs + (size_t)CH * lrs;                // CH x nr |residual|^2 of the best states
+  R* fs = (R*)(esm + lo.fs);                     // f of the final states, then the best states' energies
+  R* ebs = fs + CH;
+  R* a2 = (R*)(esm + lo.a2);                     // 4 s^2 |h_m|^2 / sigma^2
+  R* ys = (R*)(esm + lo.ys);                     // y'
+  unsigned char* Ks = esm + lo.ks;               // CH x NS
+  unsigned char* Kbs = Ks + (size_t)CH * NS;     // CH x NS
+  f32x2* Ht = (f32x2*)(esm + lo.ht);
+  __shared__ R best_e;
+  __shared__ int best_c;
+  __shared__ unsigned char dupf[1024];   // list LLRs: chain repeats an earlier chain's final state
+
+  // level rows as 16-byte pieces, np of them a row; the first chunk's ahead of everything else
+  auto stage = [&](int c0, int ch) {
+    const int np = NS >> 4, tot = ch * np;
+    for (int e = tid; e < 2 * tot; e += BS) {
+      const int e1 = e < tot ? e : e - tot, c = e1 / np, w = e1 - c * np;
+      const unsigned char* src = (e < tot ? K : Kb) + (size_t)(c0 + c) * Npad + 16 * w;
+      *(uint4*)((e < tot ? Ks : Kbs) + c * NS + 16 * w) = *(const uint4*)src;
+    }
+  };
+  stage(0, C < CH ? C : CH);
+  if constexpr (SH) {
+    int m = tid / nr, i = tid % nr;
+    const int dm = BS / nr, di = BS % nr;
+    for (int e = tid; e < nt * nr; e += BS) {
+      Ht[i * ldh + m] = f32x2{Hg[2 * (size_t)e], Hg[2 * (size_t)e + 1]};
+      m += dm;
+      i += di;
+      if (i >= nr) { i -= nr; ++m; }
+    }
+    __syncthreads();
+  }
+  auto hcol = [&](int m, int i) -> f32x2 {
+    if constexpr (SH) return Ht[i * ldh + m];
+    else return f32x2{Hg[2 * ((size_t)m * nr + i)], Hg[2 * ((size_t)m * nr + i) + 1]};
+  };
+  // y' from the first threads, the column norms from the last ones
+  for (int i = tid; i < nr; i += BS) {
+    R sr = 0, si = 0;
+#pragma unroll 8
+    for (int m = 0; m < nt; ++m) { const f32x2 v = hcol(m, i); sr += v.x - v.y; si += v.x + v.y; }
+    ys[2 * i] = y[2 * i] + s * R(Q - 1) * sr;
+    ys[2 * i + 1] = y[2 * i + 1] + s * R(Q - 1) * si;
+  }
+  for (int m = BS - 1 - tid; m < nt; m += BS) {
+    R g = 0;
+#pragma unroll 8
+    for (int i = 0; i < nr; ++i) {
+      const f32x2 v = hcol(m, i);
+      const R hr = v.x, hi = v.y;
+      g += hr * hr + hi * hi;
+    }
+    a2[m] = R(4) * s * s * g * inv_s2;
+  }
+  if (tid == 0) { best_e = R(INFINITY); best_c = 0; }
+  const int mode = a.llr_mode;
+  if (mode == 1 && a.llrs) {
+    // the list holds distinct samples: flag every chain whose first N levels equal an earlier chain's
+    const int nw = (N + 3) >> 2;
+    for (int c = tid; c < C; c += BS) {
+      const uint32_t* kc = (const uint32_t*)(K + (size_t)c * Npad);
+      bool dup = false;
+      for (int c2 = 0; c2 < c && !dup; ++c2) {
+        const uint32_t* k2 = (const uint32_t*)(K + (size_t)c2 * Npad);
+        bool same = true;
+        for (int w = 0; w < nw; ++w) {
+          const int valid = N - 4 * w;
+          const uint32_t msk = valid >= 4 ? 0xFFFFFFFFu : ((1u << (8 * valid)) - 1u);
+          same = same && ((kc[w] ^ k2[w]) & msk) == 0u;
+        }
+        dup = same;
+      }
+      dupf[c] = dup ? 1 : 0;
+    }
+  }
+
+  // Ownership: RPT marginal rows (m, kI) and a bit (m, axis, bit) per thread, or per GM (GL) threads with every
+  // GM-th (GL-th) chain each (merged at the end).  The host takes enough threads for the rows, no shape has more bits
+  // than threads, and the groups follow from the shape alone, so that the results do not depend on the launch's size.
+  const int n_rows = nt * Q, n_llr = nt * 2 * NB;
+  const int GM = a.gm, GL = a.gl, LM = BS / GM, LP = BS / GL;   // (powers of two)
+  const int gm = tid / LM, it_row = tid - gm * LM, gl = tid / LP, it_llr = tid - gl * LP;
+  const bool want_mc = a.marginals_mc != nullptr;
+  Lse2 lnum, lden;
+  int cplus = 0;
+  // row sums sum_c 2^(v_c(kQ) - Mx) (log2 units) with one running maximum Mx for the row: a point more than 2^-126
+  // below the row's largest term underflows to zero, as it would in the normalised marginal anyway
+  R Mx[RPT], sums[RPT][Q];
+  int cnt[RPT][Q];
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    Mx[r] = R(-INFINITY);
+#pragma unroll
+    for (int j = 0; j < Q; ++j) { sums[r][j] = R(0); cnt[r][j] = 0; }
+  }
+
+  for (int c0 = 0; c0 < C; c0 += CH) {
+    const int ch = C - c0 < CH ? C - c0 : CH;
+    if (c0) {
+      __syncthreads();   // (the chunk before is read)
+      stage(c0, ch);
+    }
+    __syncthreads();
+    const R s2 = R(2) * s;
+    if (a.res == 0) {
+      // a thread takes rows i and i + h2 of a chain: its levels are read (16 bytes: eight antennas) and converted once
+      // for both
+      const int h2 = (nr + 1) >> 1;
+      int c = tid / h2, i = tid - c * h2;
+      const int dc = BS / h2, di = BS - dc * h2;
+      for (int it = tid; it < ch * h2; it += BS) {
+        const unsigned char* kf = Ks + c * NS;   // (k_I, k_Q) of antenna m in bytes 2 m, 2 m + 1
+        const unsigned char* kb = Kbs + c * NS;
+        const int i1 = i + h2 < nr ? i + h2 : i;
+        R re[2] = {0, 0}, im[2] = {0, 0}, bre[2] = {0, 0}, bim[2] = {0, 0};
+        auto term = [&](int m, uint32_t f, uint32_t g) {
+          const R xr = R(f & 0xFFu), xi = R((f >> 8) & 0xFFu), br = R(g & 0xFFu), bi = R((g >> 8) & 0xFFu);
+          const f32x2 v[2] = {hcol(m, i), hcol(m, i1)};
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const R hr = v[q].x, hi = v[q].y;
+            re[q] += hr * xr - hi * xi;
+            im[q] += hr * xi + hi * xr;
+            bre[q] += hr * br - hi * bi;
+            bim[q] += hr * bi + hi * br;
+          }
+        };
+        int m = 0;
+        for (; m + 8 <= nt; m += 8) {
+          const uint4 f4 = *(const uint4*)(kf + 2 * m), g4 = *(const uint4*)(kb + 2 * m);
+          const uint32_t f[4] = {f4.x, f4.y, f4.z, f4.w}, g[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+          for (int q = 0; q < 8; ++q) term(m + q, f[q >> 1] >> (16 * (q & 1)), g[q >> 1] >> (16 * (q & 1)));
+        }
+        for (; m < nt; ++m) term(m, *(const uint16_t*)(kf + 2 * m), *(const uint16_t*)(kb + 2 * m));
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int iq = i + q * h2;
+          if (iq < nr) {
+            const R rr = ys[2 * iq] - s2 * re[q], ri = ys[2 * iq + 1] - s2 * im[q];
+            const R br = ys[2 * iq] - s2 * bre[q], bi = ys[2 * iq + 1] - s2 * bim[q];
+            rs[c * lrs + 2 * iq] = rr;
+            rs[c * lrs + 2 * iq + 1] = ri;
+            rb2[c * nr + iq] = br * br + bi * bi;
+          }
+        }
+        c += dc;
+        i += di;
+        if (i >= h2) { i -= h2; ++c; }
+      }
+    } else {
+      const int nct = (ch + 15) >> 4, nrt = (nr + 15) >> 4, ksteps = (N + 3) >> 2;
+      const int half = a.res == 2 ? ((ksteps + 1) / 2 + 1) / 2 * 2 : 1 << 30;
+      const int h = lane >> 4;
+      const bool odd = h & 1;
+      for (int u = wv; u < 2 * nct * nrt; u += NW) {
+        const int state = u & 1, rt = (u >> 1) % nrt, ct = (u >> 1) / nrt;
+        const int c = 16 * ct + (lane & 15), cc = c < ch ? c : ch - 1;
+        const unsigned char* kr = (state ? Kbs : Ks) + cc * NS;
+        const int ia = 16 * rt + (lane & 15), iac = ia < nr ? ia : nr - 1;
+        f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = re, re1 = re, im1 = re;
+        for (int st0 = 0; st0 < ksteps; st0 += 4) {
+          // (the last piece may run past N, inside the padded row; the columns there are masked)
+          const uint4 kw = *(const uint4*)(kr + 4 * st0);
+          const uint32_t w4[4] = {kw.x, kw.y, kw.z, kw.w};
+          f32x2 hv[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int m = 2 * (st0 + q) + (h >> 1);
+            hv[q] = hcol(m < nt ? m : nt - 1, iac);
+          }
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (st0 + q == half) { re1 = re; im1 = im; re = f32x4{0.f, 0.f, 0.f, 0.f}; im = re; }
+            const bool ok = 2 * (st0 + q) + (h >> 1) < nt && ia < nr;
+            const float hr = ok ? hv[q].x : 0.f, hi = ok ? hv[q].y : 0.f;
+            const float k = (float)((w4[q] >> (8 * h)) & 255u);
+            re = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? -hi : hr, k, re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f32_16x16x4f32(odd ? hr : hi, k, im, 0, 0, 0);
+          }
+        }
+        if (half < ksteps) { re = re1 + re; im = im1 + im; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int i = 16 * rt + 4 * h + j;
+          if (i < nr && c < ch) {
+            const R rr = ys[2 * i] - s2 * re[j], ri = ys[2 * i + 1] - s2 * im[j];
+            if (state) {
+              rb2[c * nr + i] = rr * rr + ri * ri;
+            } else {
+              rs[c * lrs + 2 * i] = rr;
+              rs[c * lrs + 2 * i + 1] = ri;
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();
+    // energies: the final states' from the first threads, the best states' from the last ones
+    for (int c = tid; c < ch; c += BS) {
+      R e = 0;
+#pragma unroll 16
+      for (int i = 0; i < nr; ++i)
+        e += rs[c * lrs + 2 * i] * rs[c * lrs + 2 * i] + rs[c * lrs + 2 * i + 1] * rs[c * lrs + 2 * i + 1];
+      fs[c] = -e * inv_s2;
+    }
+    for (int c = BS - 1 - tid; c < ch; c += BS) {
+      R eb = 0;
+#pragma unroll 16
+      for (int i = 0; i < nr; ++i) eb += rb2[c * nr + i];
+      ebs[c] = eb;
+    }
+    __syncthreads();
+    // Per (chain, antenna): a_n = 4 s (H^H r)_n / sigma^2 = -2 tau ln(2) g from the sampler's energy gradient at the
+    // final state, g = -2 s log2(e) H^H r / (tau sigma^2); the per-axis log normalisers over the Q levels, accumulated
+    // in log2 units; the base term.  (The residuals are done with: cm takes their place.)
+    {
+      int c = tid / nt, m = tid - c * nt;
+      const int dc = BS / nt, dm = BS - dc * nt;
+      const float* eg = (const float*)(st + so.eg) + (size_t)c0 * Npad;
+      for (int it = tid; it < ch * nt; it += BS) {
+        const R aI = kA * eg[(size_t)c * Npad + 2 * m], aQ = kA * eg[(size_t)c * Npad + 2 * m + 1];
+        const uint32_t kk = *(const uint16_t*)(Ks + c * NS + 2 * m);
+        const R sc = inv_tau * R(1.4426950408889634);
+        const R q2s = a2[m] * sc, aIs = aI * sc, aQs = aQ * sc;
+        const R kIf = (R)(kk & 255u), kQf = (R)(kk >> 8);
+        R mi = R(-INFINITY), mq = R(-INFINITY), si = R(0), sq = R(0);
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+          const R eI = R(k) - kIf, eQ = R(k) - kQf;
+          const R ti = eI * (aIs - q2s * eI), tq = eQ * (aQs - q2s * eQ);
+          // one exponential per level: of the distance to the running maximum
+          const R di = ti - mi, dq = tq - mq, xi = fex2(-fabsf(di)), xq = fex2(-fabsf(dq));
+          si = di > R(0) ? si * xi + R(1) : si + xi;
+          sq = dq > R(0) ? sq * xq + R(1) : sq + xq;
+          mi = fmaxf(mi, ti);
+          mq = fmaxf(mq, tq);
+        }
+        const R base = cw * fs[c] - (mi + flg2(si) + mq + flg2(sq)) * R(0.6931471805599453);
+        cm[c * nt + m] = f32x4{aI, aQ, base, __uint_as_float(kk)};
+        c += dc;
+        m += dm;
+        if (m >= nt) { m -= nt; ++c; }
+      }
+    }
+    if (wv == NW - 1) {
+      // the best state: smallest energy, then lowest chain
+      R be = R(INFINITY);
+      int bc = 0x7FFFFFFF;
+      for (int c = lane; c < ch; c += 64)
+        if (ebs[c] < be) { be = ebs[c]; bc = c; }
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const R oe = __shfl_xor(be, o);
+        const int oc = __shfl_xor(bc, o);
+        if (oe < be || (oe == be && oc < bc)) { be = oe; bc = oc; }
+      }
+      if (lane == 0 && be < best_e) { best_e = be; best_c = c0 + bc; }
+    }
+    __syncthreads();
+
+    // Symbol marginals and the plain Monte Carlo histogram.  For chain c the row's terms are b0 + B(kQ), the kI
+    // part b0 plus a kQ part B shared by the Q rows of antenna m, which sit in Q consecutive lanes: lane kI of the
+    // group forms the exponential of B(kQ = kI) relative to the largest B, and the group exchanges those Q
+    // values, so that a row takes two exponentials per chain.
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      const int row = it_row + r * BS;
+      if (row < n_rows) {
+        const int m = row / Q;
+        const R kt = (R)(row & (Q - 1));
+        const R q2 = a2[m];
+        const R l2e = R(1.4426950408889634), q2l = q2 * l2e;
+        for (int c = (gm - c0) & (GM - 1); c < ch; c += GM) {
+          const f32x4 v = cm[c * nt + m];
+          const uint32_t kk = __float_as_uint(v.w);
+          const R kI = (R)(kk & 255u), kQ = (R)((kk >> 8) & 255u);
+          const R eI = kt - kI, eQ = kt - kQ;
+          const R b0 = (v.z + eI * (v.x - q2 * eI)) * l2e;
+          const R bq = eQ * (v.y * l2e - q2l * eQ);       // B(kQ = kt)
+          const R bmax = group_max<Q>(bq);
+          R eqs[Q];
+          group_gather<Q>(fex2(bq - bmax), eqs);
+          const R lm = b0 + bmax;                          // the row's largest term for chain c
+          const R d = lm - Mx[r], e = fex2(-fabsf(d));
+          const bool up = d > R(0);
+          const R sc = up ? e : R(1), w = up ? R(1) : e;
+#pragma unroll
+          for (int j = 0; j < Q; ++j) sums[r][j] = sums[r][j] * sc + w * eqs[j];
+          Mx[r] = fmaxf(lm, Mx[r]);
+          if (want_mc) {
+#pragma unroll
+            for (int j = 0; j < Q; ++j) cnt[r][j] += (kI == kt && kQ == R(j)) ? 1 : 0;
+          }
+        }
+      }
+    }
+    // Bit LLRs (log2 units)
+    if (a.llrs && it_llr < n_llr) {
+      const int m = it_llr / (2 * NB), rem = it_llr - m * 2 * NB, ax = rem >= NB ? 1 : 0, bit = rem - ax * NB;
+      const int mask = 1 << (NB - 1 - bit);
+      const R q2 = a2[m] * kL2e;
+      // one loop per form (the form is uniform: no branch inside the chain loop)
+      if (mode == 0) {
+        for (int c = (gl - c0) & (GL - 1); c < ch; c += GL) {
+          const f32x4 v = cm[c * nt + m];
+          const uint32_t kk = __float_as_uint(v.w);
+          const int k = ax ? (int)(kk >> 8) : (int)(kk & 255u);
+          const R av = (ax ? v.y : v.x) * kL2e;
+          // the other value of this Gray bit: changing bit j of the label flips the binary bits j..0
+          const bool gb = ((k ^ (k >> 1)) & mask) != 0;
+          const R d = (R)((k ^ (2 * mask - 1)) - k);
+          const R f0 = fs[c] * kL2e, dl = d * (av - q2 * d);   // F of the sample, and the move's change
+          // g = (F+ - F-) / tau; F(a) = log(1 + e^a): F(g) and F(-g) share log(1 + e^-|g|)
+          const R g = (gb ? dl : -dl) * inv_tau;
+          const R l1 = flg2(R(1) + fex2(-fabsf(g)));
+          const R f1 = f0 + dl, Fp = gb ? f1 : f0, Fm = gb ? f0 : f1;
+          lnum.add(cw * Fp - (fmaxf(-g, R(0)) + l1));
+          lden.add(cw * Fm - (fmaxf(g, R(0)) + l1));
+        }
+      } else {
+        for (int c = (gl - c0) & (GL - 1); c < ch; c += GL) {
+          const uint32_t kk = __float_as_uint(cm[c * nt + m].w);
+          const int k = ax ? (int)(kk >> 8) : (int)(kk & 255u);
+          const bool plus = ((k ^ (k >> 1)) & mask) == 0;   // label bit 0 <-> b = +1
+          if (mode == 2) {
+            cplus += plus ? 1 : 0;
+          } else if (!dupf[c0 + c]) {
+            if (plus) lnum.add(fs[c] * kL2e);
+            else lden.add(fs[c] * kL2e);
+          }
+        }
+      }
+    }
+  }
+  // merge the threads' shares of a bit's and of a row's chains (through LDS, groups in order)
+  if (GL > 1) {
+    R* o = (R*)esm;
+    __syncthreads();
+    if (gl > 0 && it_llr < n_llr) {
+      R* q = o + (size_t)(gl - 1) * 5 * n_llr + it_llr;
+      q[0] = lnum.mx; q[n_llr] = lnum.sum; q[2 * n_llr] = lden.mx; q[3 * n_llr] = lden.sum;
+      q[4 * n_llr] = (R)cplus;
+    }
+    __syncthreads();
+    if (gl == 0 && it_llr < n_llr) {
+      for (int g = 1; g < GL; ++g) {
+        const R* q = o + (size_t)(g - 1) * 5 * n_llr + it_llr;
+        lnum.add(q[0], q[n_llr]);
+        lden.add(q[2 * n_llr], q[3 * n_llr]);
+        cplus += (int)q[4 * n_llr];
+      }
+    }
+  }
+  if (GM > 1) {
+    // (only shapes with one row per thread)
+    R* o = (R*)esm;
+    __syncthreads();
+    if (gm > 0 && it_row < n_rows) {
+      R* q = o + (size_t)(gm - 1) * (2 * Q + 1) * n_rows + it_row;
+      q[0] = Mx[0];
+#pragma unroll
+      for (int j = 0; j < Q; ++j) { q[(1 + j) * n_rows] = sums[0][j]; q[(1 + Q + j) * n_rows] = (R)cnt[0][j]; }
+    }
+    __syncthreads();
+    if (gm == 0 && it_row < n_rows) {
+      for (int g = 1; g < GM; ++g) {
+        const R* q = o + (size_t)(g - 1) * (2 * Q + 1) * n_rows + it_row;
+        const R om = q[0], nm = fmaxf(om, Mx[0]);
+        // (a group without chains, or of infinite distance: its largest term is -inf)
+        const R sa = Mx[0] == nm ? R(1) : fex2(Mx[0] - nm), sb = om == nm ? R(1) : fex2(om - nm);
+        Mx[0] = nm;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+          sums[0][j] = sums[0][j] * sa + q[(1 + j) * n_rows] * sb;
+          cnt[0][j] += (int)q[(1 + Q + j) * n_rows];
+        }
+      }
+    }
+  }
+  // normalise over the M points of antenna m: its Q rows sit in Q consecutive
+  // lanes of one wavefront, so the log-sum-exp is a Q-lane butterfly
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    const int row = it_row + r * BS;
+    R lv[Q];
+    R mx = R(-INFINITY);
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      lv[j] = (Mx[r] + flg2(sums[r][j])) * R(0.6931471805599453);
+      mx = lv[j] > mx ? lv[j] : mx;
+    }
+#pragma unroll
+    for (int off = 1; off < Q; off <<= 1) { const R o = __shfl_xor(mx, off); mx = o > mx ? o : mx; }
+    R sm = R(0);
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      lv[j] = fexp(lv[j] - mx);
+      sm += lv[j];
+    }
+#pragma unroll
+    for (int off = 1; off < Q; off <<= 1) sm += __shfl_xor(sm, off);
+    if (gm == 0 && row < n_rows) {
+      const R inv = R(1) / sm;
+      const size_t o = dsc.marg_off + (size_t)row * Q;
+      auto store = [&](float* dst, auto&& val) {
+        if (Q >= 4 && ((uintptr_t)dst & 15) == 0) {
+#pragma unroll
+          for (int j = 0; j + 3 < Q; j += 4) *(f32x4*)(dst + j) = f32x4{val(j), val(j + 1), val(j + 2), val(j + 3)};
+        } else {
+#pragma unroll
+          for (int j = 0; j < Q; ++j) dst[j] = val(j);
+        }
+      };
+      if (a.marginals) store(a.marginals + o, [&](int j) { return lv[j] * inv; });
+      if (want_mc) store(a.marginals_mc + o, [&](int j) { return (float)cnt[r][j] / (float)C; });
+    }
+  }
+  if (a.llrs && gl == 0 && it_llr < n_llr) {
+    R v;
+    const R clip = a.llr_clip;
+    if (mode == 0) {
+      v = lnum.value() - lden.value();
+    } else if (mode == 1) {
+      const bool hp = lnum.mx > R(-INFINITY), hm = lden.mx > R(-INFINITY);
+      v = !hp ? -clip : (!hm ? clip : lnum.value() - lden.value());
+      v = v > clip ? clip : (v < -clip ? -clip : v);
+    } else {
+      const int cm_ = C - cplus;
+      v = cm_ == 0 ? clip : (cplus == 0 ? -clip : flog(R(cplus)) - flog(R(cm_)));
+      v = v > clip ? clip : (v < -clip ? -clip : v);
+    }
+    a.llrs[dsc.llr_off + it_llr] = v;
+  }
+  // hard decision (best_c and best_e were last written before a barrier inside the chunk loop)
+  {
+    const int bc = best_c;
+    if (a.best_energy && tid == 0) a.best_energy[dsc.orig] = best_e;
+    if (a.symbols)
+      for (int m = tid; m < nt; m += BS)
+        a.symbols[dsc.sym_off + m] = Kb[(size_t)bc * Npad + 2 * m] * Q + Kb[(size_t)bc * Npad + 2 * m + 1];
+  }
+}
+
+// One instance by the path of the input type.
+template <typename R, int Q, bool SH, int BS>
+__device__ __forceinline__ void estimate_one(const EstArgs& a, const int b) {
+  if constexpr (sizeof(R) == 8) estimate_d<Q, SH>(a, b);
+  else estimate_f<Q, SH, BS, (Q == 16 && BS == 1024 ? 2 : 1)>(a, b);
+}
+
 // Direct launch (PERS false): instance blockIdx.x.  Persistent launch: items from the list, each
 // with its class's arguments.
 template <typename R, int Q, bool SH, int BS, bool PERS = false>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(BS == 256 && sizeof(R) == 4 && Q <= 8 ? 5 : 1)))
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 1 : (BS == 256 && Q <= 8 && !PERS ? 5 : 4))))
 void estimate_kernel(EstArgs a, Persist p) {
   if constexpr (!PERS) {
-    estimate_body<R, Q, SH, BS>(a, blockIdx.x);
+    estimate_one<R, Q, SH, BS>(a, blockIdx.x);
   } else {
     extern __shared__ __attribute__((aligned(16))) unsigned char esm[];
     for (;;) {
@@ -605,62 +1016,74 @@ void estimate_kernel(EstArgs a, Persist p) {
       if (it >= p.n_items) break;
       const WorkItem w = p.items[it];
       const EstArgs ca = ((const EstArgs*)p.cls)[__builtin_amdgcn_readfirstlane(w.cls)];
-      estimate_body<R, Q, SH, BS>(ca, __builtin_amdgcn_readfirstlane(w.inst));
+      estimate_one<R, Q, SH, BS>(ca, __builtin_amdgcn_readfirstlane(w.inst));
     }
     persist_done(p);
   }
 }
 
-size_t estimate_lds_bytes(int nt, int nr, int M, int N, int chunk, bool fp64) {
-  const size_t R = fp64 ? 8 : 4;
-  const size_t cm = fp64 ? 32 : 20;
-  return cm * (size_t)chunk * nt + R * (3 * (size_t)chunk * nr + 4 * (size_t)chunk + nt + 2 * (size_t)nr) +
-         2 * (size_t)chunk * N + 16;
+// LDS of the float64 path without H.
+static size_t estimate_lds_bytes(int nt, int nr, int N, int chunk) {
+  return 32 * (size_t)chunk * nt + 8 * (3 * (size_t)chunk * nr + 4 * (size_t)chunk + nt + 2 * (size_t)nr) + 2 * (size_t)chunk * N + 16;
 }
 
-// Chains per chunk (LDS budget 96 KiB).  When the (antenna, kI) rows outnumber
-// the 256 threads and there are several chunks, the chunks are staged again
-// for every block of rows.
 // H is staged in LDS when it fits 64 KiB (transposed, padded rows).
 static bool estimate_h_in_lds(int nt, int nr, bool fp64) {
   return 2 * (size_t)(nt + 1) * nr * (fp64 ? 8 : 4) <= 65536;
 }
 
 // Threads per workgroup: one (antenna, kI) row each, in 256, 512 or 1024 threads; 1024 whenever H is
-// read from global memory (the residual and H^H r sweeps, O(C nt nr), then dominate).  The float64
+// read from global memory.  Launches of at most one workgroup per CU take 1024 threads, which shorten every phase but
+// the rows': 256 problems of 32x32 64-QAM, 64 chains, 47 us, 257 of them in 256 threads each 60 us.  The float64
 // path (nt <= 32) keeps 256.
-static int estimate_threads(int nt, int nr, int Q, bool fp64) {
+static int estimate_threads(int nt, int nr, int Q, bool fp64, int n_inst) {
   if (fp64) return 256;
-  if (!estimate_h_in_lds(nt, nr, false) || nt * Q > 512) return 1024;
+  if (!estimate_h_in_lds(nt, nr, false) || nt * Q > 512 || n_inst <= 256) return 1024;
   return nt * Q > 256 ? 512 : 256;
 }
 
-int estimate_chunk(int nt, int nr, int M, int N, int C, bool fp64) {
+// Threads that share a row's (a bit's) chains, of those that a large launch gives the shape.
+static void estimate_groups(int nt, int nr, int Q, int* gm, int* gl) {
+  const int NB = Q == 2 ? 1 : (Q == 4 ? 2 : (Q == 8 ? 3 : 4)), th = estimate_threads(nt, nr, Q, false, 1 << 30);
+  *gm = est_groups(nt * Q, th < 512 ? th : 512);
+  *gl = est_groups(nt * 2 * NB, th);
+}
+
+static size_t estimate_lds(int nt, int nr, int Q, int N, int chunk, bool fp64) {
+  const bool sh = estimate_h_in_lds(nt, nr, fp64);
+  if (fp64) return estimate_lds_bytes(nt, nr, N, chunk) + (sh ? 2 * (size_t)(nt + 1) * nr * 8 + 16 : 0);
+  int gm, gl;
+  estimate_groups(nt, nr, Q, &gm, &gl);
+  return est_lds(nt, nr, Q, N, chunk, gm, gl, sh).end;
+}
+
+// Chains per chunk: all of them where they fit 128 KiB of LDS (96 KiB with 256 or 512 threads, whose
+// workgroups share a CU); 256-thread workgroups run five per CU when their LDS fits 32 KiB, 512-thread ones two
+// per CU within 80 KiB: the smaller chunk that gets there, if it keeps at least 16 chains.
+static int estimate_chunk(int nt, int nr, int Q, int N, int C, bool fp64, int threads) {
+  const size_t most = (!fp64 && threads == 1024 ? 128 : 96) * 1024;   // (float64: beside H)
   int ch = C;
-  while (ch > 1 && estimate_lds_bytes(nt, nr, M, N, ch, fp64) > 96 * 1024) ch = (ch + 1) / 2;
-  // 256-thread workgroups run five per CU when their LDS (with H staged) fits 32 KiB, 512-thread
-  // ones two per CU within 80 KiB: take the smaller chunk that gets there, if it keeps at least
-  // 16 chains
-  const int Q = M <= 4 ? 2 : (M <= 16 ? 4 : (M <= 64 ? 8 : 16));
-  const int bs = estimate_threads(nt, nr, Q, fp64);
-  if (!fp64 && bs <= 512) {
-    const size_t budget = (bs == 256 ? 32 : 80) * 1024;
-    const size_t hx = 2 * (size_t)(nt + 1) * nr * sizeof(float) + 16;   // H is in LDS (bs < 1024)
+  while (ch > 1 && (fp64 ? estimate_lds_bytes(nt, nr, N, ch) : estimate_lds(nt, nr, Q, N, ch, false)) > most)
+    ch = (ch + 1) / 2;
+  if (!fp64 && threads <= 512) {
+    const size_t budget = (threads == 256 ? 32 : 80) * 1024;
     int c2 = ch;
-    while (c2 > 16 && estimate_lds_bytes(nt, nr, M, N, c2, false) + hx > budget) c2 = (c2 + 1) / 2;
-    if (estimate_lds_bytes(nt, nr, M, N, c2, false) + hx <= budget) ch = c2;
+    while (c2 > 16 && estimate_lds(nt, nr, Q, N, c2, false) > budget) c2 = (c2 + 1) / 2;
+    if (estimate_lds(nt, nr, Q, N, c2, false) <= budget) ch = c2;
   }
   return ch;
 }
 
 template <typename R, int Q, int BS>
 static hipError_t launch_eb(const EstArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {
-  const size_t hbytes = 2 * (size_t)(a.nt + 1) * a.nr * sizeof(R);
   const bool sh = estimate_h_in_lds(a.nt, a.nr, sizeof(R) == 8);
-  const size_t lds = estimate_lds_bytes(a.nt, a.nr, Q * Q, a.N, a.chunk, a.fp64) + (sh ? hbytes + 16 : 0);
+  const size_t lds = estimate_lds(a.nt, a.nr, Q, a.N, a.chunk, sizeof(R) == 8);
   void (*k)(EstArgs, Persist);
-  if (p || cfg) k = sh ? estimate_kernel<R, Q, true, BS, true> : estimate_kernel<R, Q, false, BS, true>;
-  else k = sh ? estimate_kernel<R, Q, true, BS> : estimate_kernel<R, Q, false, BS>;
+  // (the smaller workgroups only run with H in LDS)
+  constexpr bool kGlob = BS == 1024 || sizeof(R) == 8;
+  if (!sh && !kGlob) return hipErrorInvalidConfiguration;
+  if (p || cfg) k = sh ? estimate_kernel<R, Q, true, BS, true> : estimate_kernel<R, Q, !kGlob, BS, true>;
+  else k = sh ? estimate_kernel<R, Q, true, BS> : estimate_kernel<R, Q, !kGlob, BS>;
   if (cfg) {
     cfg->k = (const void*)k;
     cfg->threads = BS;
@@ -685,7 +1108,7 @@ static hipError_t launch_e(const EstArgs& a, hipStream_t s, const Persist* p, in
   if constexpr (sizeof(R) == 8) {
     return launch_eb<R, Q, 256>(a, s, p, gn, cfg);
   } else {
-    const int bs = estimate_threads(a.nt, a.nr, Q, false);
+    const int bs = a.threads;
     return bs == 256 ? launch_eb<R, Q, 256>(a, s, p, gn, cfg)
                      : (bs == 512 ? launch_eb<R, Q, 512>(a, s, p, gn, cfg) : launch_eb<R, Q, 1024>(a, s, p, gn, cfg));
   }
@@ -700,6 +1123,29 @@ static hipError_t launch_r(const EstArgs& a, hipStream_t s, const Persist* p, in
     case 16: return launch_e<R, 16>(a, s, p, gn, cfg);
   }
   return hipErrorInvalidValue;
+}
+
+// The order of the residual sums of a shape with C chains (EstArgs::res), whatever the launch's size: one
+// thread per sum for the shapes of at most 256 marginal rows, matrix cores for the others, their K steps in two halves
+// where the chains that fit 96 KiB of LDS with 20 bytes per (chain, antenna) make at most 8 tiles for a workgroup's 16
+// waves.  (Any one order would do; changing a shape's moves its marginals by up to 1e-2 where |f| is 1e5.)
+static int estimate_res(int nt, int nr, int Q, int C, bool fp64) {
+  const int bs = estimate_threads(nt, nr, Q, fp64, 1 << 30);
+  if (fp64 || bs == 256) return 0;
+  if (bs == 512) return 1;
+  int ch = C;
+  while (ch > 1 && 20 * (size_t)ch * nt + 4 * (3 * (size_t)ch * nr + 4 * (size_t)ch + nt + 2 * (size_t)nr) + 4 * (size_t)ch * nt + 16 > 96 * 1024)
+    ch = (ch + 1) / 2;
+  const int units = ((nr + 15) / 16) * ((ch + 15) / 16);
+  return 2 * units <= 16 && (size_t)units * 4096 <= (size_t)ch * nt * 20 ? 2 : 1;
+}
+
+void estimate_shape(EstArgs* ea, int nt, int nr, int M, int N, int C, bool fp64, int n_inst) {
+  const int Q = M <= 4 ? 2 : (M <= 16 ? 4 : (M <= 64 ? 8 : 16));
+  ea->threads = estimate_threads(nt, nr, Q, fp64, n_inst);
+  ea->res = estimate_res(nt, nr, Q, C, fp64);
+  ea->chunk = estimate_chunk(nt, nr, Q, N, C, fp64, ea->threads);
+  estimate_groups(nt, nr, Q, &ea->gm, &ea->gl);
 }
 
 hipError_t launch_estimate(const EstArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {

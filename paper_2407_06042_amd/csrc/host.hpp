@@ -15,6 +15,7 @@ struct Plan {
   size_t inst_off, state_off, wscratch_off, total;
   double tau, am, bm, gm;
   bool naive;
+  int n_beside;       // instances of all classes that run beside this one's (a plan), 0: its own alone
   uint32_t mix_thr;   // learned mixture: plain kernel iff the 24-bit uniform < mix_thr
 };
 

@@ -114,6 +114,7 @@ dmala_status class_plan(dmala_plan_s* P, ClassInfo& c) {
   p.wg_chain_blocks = c.cbw;
   const dmala_status st = make_plan(c.count, c.shape.nt, c.shape.nr, c.shape.qam_order, &p, c.pl);
   c.pl.sh.share = 1;
+  c.pl.n_beside = P->n_inst;
   // (the classes share the GPU: spread over more waves when all of them together leave it room)
   if (!P->spread) c.pl.sh.spread = 0;
   return st;

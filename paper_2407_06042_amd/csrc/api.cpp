@@ -111,11 +111,9 @@ dmala_status make_plan(int32_t n_inst, int32_t nt, int32_t nr, int32_t M, const 
   sh.spread = p->tile_config == 0 && p->wg_chain_blocks == 0 && sampler_load(sh, n_inst) <= 1.0 ? 1 : 0;
   sh.inst_bytes = round_up(kParamBytes + sh.frag_bytes, 256);
   sh.state_bytes = state_offsets(sh.Cpad, sh.Npad).end;
-  sh.wscratch_bytes = setup_w_global(nt) ? round_up((size_t)nt * (nt + 1) * 16, 256) : 0;
   pl.inst_off = 0;
   pl.state_off = round_up((size_t)n_inst * sh.inst_bytes, 256);
-  pl.wscratch_off = round_up(pl.state_off + (size_t)n_inst * sh.state_bytes, 256);
-  pl.total = pl.wscratch_off + (size_t)n_inst * sh.wscratch_bytes;
+  pl.total = round_up(pl.state_off + (size_t)n_inst * sh.state_bytes, 256);
   pl.tau = p->tau > 0 ? p->tau : 2.0;
   pl.am = p->alpha_mult > 0 ? p->alpha_mult : 1.0;
   pl.bm = p->beta_mult > 0 ? p->beta_mult : 1.0;
@@ -154,8 +152,8 @@ void make_args(const void* H, const void* y, const void* sigma2, int32_t n_inst,
   sa.sigma2_val = sigma2_val;
   sa.status = (!eval_out && out) ? out->status : nullptr;
   sa.ws_inst = base + pl.inst_off; sa.inst_stride = sh.inst_bytes;
-  sa.wscratch = base + pl.wscratch_off; sa.wscratch_stride = sh.wscratch_bytes;
-  sa.n_inst = n_inst; sa.nt = sh.nt; sa.nr = sh.nr; sa.Q = sh.Q; sa.N = sh.N; sa.Npad = sh.Npad;
+  sa.n_inst = n_inst; sa.n_all = pl.n_beside > n_inst ? pl.n_beside : n_inst;
+  sa.nt = sh.nt; sa.nr = sh.nr; sa.Q = sh.Q; sa.N = sh.N; sa.Npad = sh.Npad;
   sa.RT = sh.RT; sa.KB = sh.KB; sa.fp64 = sh.fp64; sa.pm = sh.pm; sa.naive = pl.naive ? 1 : 0; sa.cx = sh.cx;
   sa.tau = pl.tau; sa.alpha_mult = pl.am; sa.beta_mult = pl.bm; sa.gamma_mult = pl.gm;
 

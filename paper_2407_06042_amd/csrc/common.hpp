@@ -73,7 +73,6 @@ struct Shape {
   size_t inst_bytes;   // per-instance setup block
   size_t frag_bytes;   // MFMA fragments (MFMA path)
   size_t state_bytes;  // per-instance sampler->estimator block
-  size_t wscratch_bytes;  // per-instance setup working matrix (large nt)
 };
 
 // Offsets inside the per-instance state block.
@@ -128,9 +127,9 @@ struct SetupArgs {
   double sigma2_val;   // the noise variance of every instance when sigma2 is NULL
   int32_t* status;     // optional [caller's instance index]: 0, or DMALA_ERR_NONFINITE for a flagged instance
   unsigned char* ws_inst; size_t inst_stride;
-  unsigned char* wscratch; size_t wscratch_stride;  // per-instance working matrix when nt > 32
   int n_inst, nt, nr, Q, N, Npad, RT, KB, fp64, pm, naive;
   int cx;              // 1: pack the matrices as complex planes (the sampler's complex-plane layouts)
+  int n_all;           // instances that are set up beside one another (a plan's, all classes)
   double tau, alpha_mult, beta_mult, gamma_mult;
 };
 
@@ -195,6 +194,37 @@ __device__ inline int persist_take(const Persist& p, unsigned char* lds) {
   return __builtin_amdgcn_readfirstlane(slot[0]);
 }
 
+// A class's arguments, in scalar registers (constant address space) and with their pointers known to be global: read
+// through an ordinary pointer they take vector registers and flat accesses, and every branch on a size becomes a
+// masked one.
+template <typename T> __device__ __forceinline__ T persist_args_words(const void* cls, int i) {
+  struct Words { uint32_t w[sizeof(T) / 4]; } r;
+  static_assert(sizeof(Words) == sizeof(T), "whole words");
+  const __attribute__((address_space(4))) uint32_t* s =
+      (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)cls + (size_t)i * (sizeof(T) / 4);
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(T) / 4); ++k) r.w[k] = s[k];
+  return __builtin_bit_cast(T, r);
+}
+template <typename T> __device__ __forceinline__ void as_global(T*& p) { p = (T*)(__attribute__((address_space(1))) T*)p; }
+__device__ __forceinline__ void as_global(SetupArgs& a) {
+  as_global(a.desc); as_global(a.H); as_global(a.y); as_global(a.sigma2); as_global(a.status); as_global(a.ws_inst);
+}
+__device__ __forceinline__ void as_global(SamplerArgs& a) {
+  as_global(a.desc); as_global(a.ws_inst); as_global(a.ws_state); as_global(a.final_state); as_global(a.accept_count);
+  as_global(a.trace_accept); as_global(a.trace_hash); as_global(a.mlp); as_global(a.train_rows);
+  as_global(a.x_from); as_global(a.x_to); as_global(a.eval_out); as_global(a.eval_dim);
+}
+__device__ __forceinline__ void as_global(EstArgs& a) {
+  as_global(a.desc); as_global(a.H); as_global(a.y); as_global(a.sigma2); as_global(a.ws_inst); as_global(a.ws_state);
+  as_global(a.symbols); as_global(a.marginals); as_global(a.llrs); as_global(a.best_energy); as_global(a.marginals_mc);
+}
+template <typename T> __device__ __forceinline__ T persist_args(const void* cls, int i) {
+  T a = persist_args_words<T>(cls, i);
+  as_global(a);
+  return a;
+}
+
 // The workgroup has taken its last item; the last one to get here resets the counters.
 __device__ inline void persist_done(const Persist& p) {
   if (threadIdx.x == 0) {
@@ -221,7 +251,6 @@ struct KernelCfg {
 // p->items set) they make a persistent launch of p->n_items items on `grid` workgroups.
 hipError_t launch_setup(const SetupArgs& a, hipStream_t s, const Persist* p = nullptr, int grid = 0,
                         KernelCfg* cfg = nullptr);
-bool setup_w_global(int nt);
 hipError_t launch_sampler(const Shape& sh, const SamplerArgs& a, bool eval, hipStream_t s, const Persist* p = nullptr,
                           int grid = 0, KernelCfg* cfg = nullptr);
 hipError_t launch_estimate(const EstArgs& a, hipStream_t s, const Persist* p = nullptr, int grid = 0,

@@ -12,7 +12,7 @@ namespace host {
 // Workspace layout and launch geometry of one uniform batch (one shape class).
 struct Plan {
   Shape sh;
-  size_t inst_off, state_off, wscratch_off, total;
+  size_t inst_off, state_off, total;
   double tau, am, bm, gm;
   bool naive;
   int n_beside;       // instances of all classes that run beside this one's (a plan), 0: its own alone

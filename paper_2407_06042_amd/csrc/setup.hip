@@ -1,10 +1,11 @@
 // Instance setup: Gram matrix, matched filter, preconditioner and packing.
 //
-// One workgroup per instance, float64 arithmetic.  Computes in the complex
+// One workgroup per instance, float64 arithmetic, bound by latency (waits for H, the pivots of the inverse, barriers;
+// launch_setup chooses how many instances share a CU against that).  Computes in the complex
 // form (the real-equivalent matrices of eq. sys_model are expanded only when
 // packing):
 //   G = H^H H, z = H^H y, ||y||^2                      (gradient of eq. grad: grad f = -(2/sigma^2)(Gx - z))
-//   M = (G + gamma I)^-1 by in-place Gauss-Jordan       (preconditioner of the Remark after Algorithm 1;
+//   M = (G + gamma I)^-1 by blocked Gauss-Jordan        (preconditioner of the Remark after Algorithm 1;
 //                                                         G + gamma I is Hermitian positive definite, so no pivoting)
 //   A = M G = I - gamma M,  b = M z                     (so that M grad f = -(2/sigma^2)(A x - b))
 // and writes, scaled to the index units of the sampler (see common.hpp),
@@ -29,13 +30,31 @@ __device__ __forceinline__ cd cadd(cd a, cd b) { return {a.re + b.re, a.im + b.i
 __device__ __forceinline__ cd cmul(cd a, cd b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 __device__ __forceinline__ cd cconjmul(cd a, cd b) { return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re}; }
 
-// Entry (n, n2) of the interleaved real-equivalent of complex X (leading dimension ld).
-__device__ __forceinline__ double realeq(const cd* X, int ld, int n, int n2) {
-  const cd v = X[(n >> 1) * ld + (n2 >> 1)];
-  const int a = n & 1, b = n2 & 1;
-  return (a == b) ? v.re : (a == 0 ? -v.im : v.im);
-}
 __device__ __forceinline__ double realeq_vec(const cd* v, int n) { return (n & 1) ? v[n >> 1].im : v[n >> 1].re; }
+
+// Hermitian matrices (G, M) are held as the 16 x 16 tiles (i, j), i <= j, of their nb x nb tile grid, tile rows of 16
+// entries with entry c of row r at r ^ c: the 16 lanes that read one row, one column, or the rows of a column of an
+// accumulator reach different LDS banks.
+__host__ __device__ constexpr int tile_count(int nb) { return nb * (nb + 1) / 2; }
+__device__ __forceinline__ int tile_index(int nb, int i, int j) { return i * (2 * nb - i - 1) / 2 + j; }
+
+// Entry (r, c) of tile (i, j) of X, any i and j.  SUB: of I - g X instead.
+template <bool SUB>
+__device__ __forceinline__ cd tile_entry(const cd* X, int nb, double g, int i, int j, int r, int c) {
+  cd e;
+  if (i <= j) {
+    e = X[tile_index(nb, i, j) * 256 + 16 * r + (r ^ c)];
+  } else {
+    e = X[tile_index(nb, j, i) * 256 + 16 * c + (r ^ c)];
+    e.im = -e.im;
+  }
+  if constexpr (SUB) e = {(i == j && r == c ? 1.0 : 0.0) - g * e.re, -g * e.im};
+  return e;
+}
+template <bool SUB>
+__device__ __forceinline__ cd mat_entry(const cd* X, int nb, double g, int m, int m2) {
+  return tile_entry<SUB>(X, nb, g, m >> 4, m2 >> 4, m & 15, m2 & 15);
+}
 
 // Value of v in lane `lane` of the wavefront (lane uniform).
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
@@ -44,25 +63,63 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
   const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-
-// Four complex entries 16 TPR bytes apart from LDS address a, waited for in
-// the same block: the Gauss-Jordan update keeps four row entries in flight
-// (the compiler would otherwise load all of them at once and spill the matrix).
-typedef double d2v __attribute__((ext_vector_type(2)));
-typedef double d4 __attribute__((ext_vector_type(4)));
-template <int TPR>
-__device__ __forceinline__ void lds_read4(uint32_t a, d2v (&r)[4]) {
-  asm volatile(
-      "ds_read2_b64 %0, %4 offset1:1\n\t"
-      "ds_read2_b64 %1, %4 offset0:%5 offset1:%6\n\t"
-      "ds_read2_b64 %2, %4 offset0:%7 offset1:%8\n\t"
-      "ds_read2_b64 %3, %4 offset0:%9 offset1:%10\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
-      : "v"(a), "i"(2 * TPR), "i"(2 * TPR + 1), "i"(4 * TPR), "i"(4 * TPR + 1), "i"(6 * TPR), "i"(6 * TPR + 1)
-      : "memory");
+// Value of v in lane P of each group of 16 lanes (row_newbcast).
+template <int P>
+__device__ __forceinline__ double bcast16(double v) {
+  return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + P, 0xf, 0xf, false);
+}
+// The 16 lanes of group G (of four), copied to every group.
+template <int G>
+__device__ __forceinline__ unsigned group16(unsigned v) {
+  const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  const unsigned x = h[G >> 1];
+  const auto q = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return q[G & 1];
+}
+template <int G>
+__device__ __forceinline__ double group16(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = group16<G>((unsigned)u), hi = group16<G>((unsigned)(u >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// In-place Gauss-Jordan inverse of a Hermitian positive definite 16 x 16 tile in one wavefront's registers, in the
+// accumulator layout (lane l, element j: row l / 16 + 4 j, column l % 16), pivots 0 .. lim - 1 (the rest is the identity).
+// Pivots are real.  Step p: column p by a lane broadcast, row p by two swaps between the lane groups, no LDS.
+template <int P>
+__device__ __forceinline__ void invert_step(double (&re)[4], double (&im)[4], int lane) {
+  constexpr int J = P >> 2, G = P & 3;
+  const double piv = readlane_f64(re[J], 16 * G + P);
+  // reciprocal by Newton steps from the hardware's estimate
+  double inv = __builtin_amdgcn_rcp(piv);
+  inv = fma(fma(-piv, inv, 1.0), inv, inv);
+  inv = fma(fma(-piv, inv, 1.0), inv, inv);
+  const bool pc = (lane & 15) == P, pr = (lane >> 4) == G;
+  double rr = group16<G>(re[J]), ri = group16<G>(im[J]);
+  rr = pc ? inv : rr * inv;
+  ri = pc ? 0.0 : ri * inv;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const double cr = bcast16<P>(re[j]), ci = bcast16<P>(im[j]);
+    const double br = pc ? 0.0 : re[j], bi = pc ? 0.0 : im[j];
+    const double nr = fma(-cr, rr, fma(ci, ri, br)), ni = fma(-cr, ri, fma(-ci, rr, bi));
+    re[j] = j == J && pr ? rr : nr;
+    im[j] = j == J && pr ? ri : ni;
+  }
+}
+template <int P>
+__device__ __forceinline__ void invert_from(double (&re)[4], double (&im)[4], int lane, int lim) {
+  if constexpr (P < 16) {
+    if (P < lim) {
+      invert_step<P>(re, im, lane);
+      invert_from<P + 1>(re, im, lane, lim);
+    }
+  }
+}
+
+enum { kSigma2, kStep, kGamma, kCE, kCz, kCP, kCb, kYY, kNonfinite, kConsts };   // constants kept in LDS
 constexpr int kRedSlots = 16;   // one per wavefront of a workgroup of up to 1024 threads
 
 // Sum (or maximum) of v over the workgroup, returned to every thread: a butterfly within each
@@ -90,7 +147,7 @@ __device__ __forceinline__ float via_float(double v) {
   return f;
 }
 
-// Pack c * R(X) (N x N, zero-padded to Npad) into MFMA fragments.
+// Pack c * R(Y) (N x N, zero-padded to Npad) into MFMA fragments, Y = X or (SUB) I - g X.
 // npass = 3 (fp16 lo, mid, hi), 2 (fp16 lo, hi) or 1 (fp16 or bf16 when bf16 != 0);
 // the terms are stored in accumulation order, small terms first.
 // Fragment (pass p, row tile rt, K block kb) lane l element j holds entry
@@ -99,20 +156,19 @@ __device__ __forceinline__ float via_float(double v) {
 // the B operand from its own registers.
 // With cx != 0 the complex planes are packed instead (the sampler's complex-plane layouts): pass p,
 // plane pl (real, imaginary), antenna tile at (16 rows), K block kb of 32 antennas; lane l element j
-// holds plane(X)[16 at + l%16][16 (2 kb + j/4) + 4 (l/16) + j%4] -- the same K permutation over
+// holds plane(Y)[16 at + l%16][16 (2 kb + j/4) + 4 (l/16) + j%4] -- the same K permutation over
 // antennas that the real-equivalent packing applies to real dimensions.
 // The form (NPASS terms, bf16, complex planes) is a compile-time choice and the function is inlined,
 // so that the element loop has no branches and X keeps its address space (LDS reads, not flat loads).
-template <int NPASS, bool BF16, bool CX>
-__device__ __forceinline__ float pack_fragments(const cd* X, int ld, double c, int nt, int N, int RT, int KB,
+template <int NPASS, bool BF16, bool CX, bool SUB>
+__device__ __forceinline__ float pack_fragments(const cd* X, int tid, int nb, double g, double c, int nt, int RT, int KB,
                                                 unsigned char* dst) {
-  constexpr int npass = NPASS;
-  constexpr bool bf16 = BF16, cx = CX;
-  // X is Hermitian positive semidefinite (G, and A = I - gamma M, whose eigenvalues lie in [0, 1)),
-  // so |Re x_ij|, |Im x_ij| <= |x_ij| <= sqrt(x_ii x_jj) <= max_i x_ii: the largest entry is the
+  constexpr bool cx = CX;
+  // Y is Hermitian positive semidefinite (G, and A = I - gamma M, whose eigenvalues lie in [0, 1)),
+  // so |Re y_ij|, |Im y_ij| <= |y_ij| <= sqrt(y_ii y_jj) <= max_i y_ii: the largest entry is the
   // largest diagonal one.  Every wavefront reads the diagonal and reduces it for itself (no barrier).
   double mx = 0.0;
-  for (int i = threadIdx.x & 63; i < nt; i += 64) mx = fmax(mx, fabs(X[i * ld + i].re));
+  for (int i = tid & 63; i < nt; i += 64) mx = fmax(mx, fabs(mat_entry<SUB>(X, nb, g, i, i).re));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
   mx *= fabs(c);
@@ -122,122 +178,152 @@ __device__ __forceinline__ float pack_fragments(const cd* X, int ld, double c, i
   const double sc = ldexp(c, e2);
   const int AT = RT / 2, KBX = RT / 4;
   const size_t pass_stride = cx ? (size_t)2 * AT * KBX * 1024 : (size_t)RT * KB * 1024;
-  const int items = (int)(pass_stride / 16);
-  for (int it = threadIdx.x; it < items; it += blockDim.x) {
-    const int l = it & 63;
-    const int t = it >> 6;
-    // real-equivalent: (row tile, K block); complex planes: (plane, antenna tile, K block)
-    const int kb = cx ? t % KBX : t % KB;
-    const int rt = cx ? (t / KBX) % AT : t / KB;
-    const int pl = cx ? t / (KBX * AT) : 0;
-    const int n = 16 * rt + (l & 15);
-    union { _Float16 h[8]; __bf16 b[8]; uint4 u; } f0, f1, f2;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int n2 = 16 * (2 * kb + (j >> 2)) + 4 * (l >> 4) + (j & 3);
-      double v;
-      if constexpr (cx) {
-        const cd e = X[(n < nt && n2 < nt ? n : 0) * ld + (n2 < nt ? n2 : 0)];
-        v = (n < nt && n2 < nt) ? sc * (pl ? e.im : e.re) : 0.0;
-      } else {
-        v = (n < N && n2 < N) ? sc * realeq(X, ld, n, n2) : 0.0;
-      }
-      if constexpr (bf16) {
-        f0.b[j] = (__bf16)via_float(v);
+  // a wavefront packs one fragment at a time (cx: both planes of it), so that the tile is uniform
+  const int nfrag = cx ? AT * KBX : RT * KB;
+  const int l = tid & 63, lr = l & 15, lg = l >> 4;
+  for (int t = __builtin_amdgcn_readfirstlane(tid >> 6); t < nfrag; t += blockDim.x >> 6) {
+    const int kb = cx ? t % KBX : t % KB, rt = cx ? t / KBX : t / KB;
+    union Frag { _Float16 h[8]; __bf16 b[8]; uint4 u; };
+    Frag f[cx ? 2 : 1][NPASS];
+    auto put = [&](Frag (&o)[NPASS], int j, double v) {
+      if constexpr (BF16) {
+        o[0].b[j] = (__bf16)via_float(v);
       } else {
         const _Float16 hi = (_Float16)via_float(v);
         const double r1 = v - (double)hi;
         const _Float16 mid = (_Float16)via_float(r1);
         const double r2 = r1 - (double)mid;
-        if constexpr (npass == 3) { f0.h[j] = (_Float16)via_float(r2); f1.h[j] = mid; f2.h[j] = hi; }
-        else if constexpr (npass == 2) { f0.h[j] = mid; f1.h[j] = hi; }
-        else f0.h[j] = hi;
+        o[NPASS - 1].h[j] = hi;
+        if constexpr (NPASS > 1) o[NPASS - 2].h[j] = mid;
+        if constexpr (NPASS > 2) o[0].h[j] = (_Float16)via_float(r2);
+      }
+    };
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int ct = 2 * kb + q;   // tile column (cx), or half of one
+      if constexpr (cx) {
+        const int n = 16 * rt + lr;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int n2 = 16 * ct + 4 * lg + j;
+          cd e = {0.0, 0.0};
+          if (rt < nb && ct < nb) e = tile_entry<SUB>(X, nb, g, rt, ct, lr, 4 * lg + j);
+          const bool ok = n < nt && n2 < nt;
+          put(f[0], 4 * q + j, ok ? sc * e.re : 0.0);
+          put(f[1], 4 * q + j, ok ? sc * e.im : 0.0);
+        }
+      } else {
+        const int m = 8 * rt + (lr >> 1);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int m2 = 8 * ct + 2 * lg + j;
+          cd e = {0.0, 0.0};
+          if ((rt >> 1) < nb && (ct >> 1) < nb) e = tile_entry<SUB>(X, nb, g, rt >> 1, ct >> 1, m & 15, m2 & 15);
+          const bool ok = m < nt && m2 < nt;
+          const double vr = ok ? sc * e.re : 0.0, vi = ok ? sc * e.im : 0.0;
+          // real-equivalent rows (Re, Im): [re -im; im re]
+          put(f[0], 4 * q + 2 * j, (lr & 1) ? vi : vr);
+          put(f[0], 4 * q + 2 * j + 1, (lr & 1) ? vr : -vi);
+        }
       }
     }
-    unsigned char* o = dst + (size_t)t * 1024 + l * 16;
-    *(uint4*)o = f0.u;
-    if constexpr (npass > 1) *(uint4*)(o + pass_stride) = f1.u;
-    if constexpr (npass > 2) *(uint4*)(o + 2 * pass_stride) = f2.u;
+#pragma unroll
+    for (int pl = 0; pl < (cx ? 2 : 1); ++pl) {
+      // cx: plane, antenna tile, K block
+      unsigned char* o = dst + (size_t)(cx ? pl * nfrag + t : t) * 1024 + l * 16;
+#pragma unroll
+      for (int ps = 0; ps < NPASS; ++ps) *(uint4*)(o + ps * pass_stride) = f[pl][ps].u;
+    }
   }
   return (float)ldexp(1.0, -e2);
 }
 
-// Dense row-major double copy of c * R(X), zero-padded to Npad x Npad.
-__device__ void pack_dense(const cd* X, int ld, double c, int N, int Npad, double* dst) {
+// Dense row-major double copy of c * R(Y), zero-padded to Npad x Npad.
+template <bool SUB>
+__device__ void pack_dense(const cd* X, int nb, double g, double c, int N, int Npad, double* dst) {
   for (int e = threadIdx.x; e < Npad * Npad; e += blockDim.x) {
-    const int n = e / Npad, n2 = e % Npad;
-    dst[e] = (n < N && n2 < N) ? c * realeq(X, ld, n, n2) : 0.0;
+    const int n = e / Npad, n2 = e % Npad, p = n & 1, p2 = n2 & 1;
+    double v = 0.0;
+    if (n < N && n2 < N) {
+      const cd x = mat_entry<SUB>(X, nb, g, n >> 1, n2 >> 1);
+      v = c * (p == p2 ? x.re : (p == 0 ? -x.im : x.im));
+    }
+    dst[e] = v;
   }
 }
 
-// Working-matrix placement and thread counts (launch_setup): up to 64 antennas 256 threads with the
-// matrix in LDS (up to about 75 KiB: two workgroups per CU), beyond that 1024 threads with the
-// matrix in this instance's slice of the workspace.
-// RMAX: rows of the working matrix the Gauss-Jordan register layout covers (threads per row BS / RMAX).
-template <typename TIn, bool WGLOB, int BS, int RMAX>
+// LDS: a region for the matrix's tiles, the staged chunk of H (before them) and the panels of the Gauss-Jordan sweep
+// (between the two packings), then z and b, then kRedSlots partials of block_reduce and
+// the instance's constants.
+__host__ __device__ constexpr int setup_chunk(int rmax) { return rmax <= 32 ? 16 : 32; }
+inline size_t setup_lds_bytes(int nt, int rmax) {
+  const int nb = (nt + 15) / 16;
+  size_t region = (size_t)tile_count(nb) * 4096;
+  const size_t stage = ((size_t)setup_chunk(rmax) * (nt + 1) + 16) * sizeof(cd), panels = nb > 1 ? (3 * (size_t)(nb - 1) + 1) * 4096 : 0;
+  region = stage > region ? stage : region;
+  region = panels > region ? panels : region;
+  return region + 2 * (size_t)nt * sizeof(cd) + (kRedSlots + kConsts) * sizeof(double);
+}
+
+// RMAX: largest number of antennas.
+template <typename TIn, int BS, int RMAX>
 __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
-  const int tid = threadIdx.x, nt = a.nt, nr = a.nr, N = a.N, Npad = a.Npad;
-  const int ld = nt + 1;  // padded leading dimension of the matrices (no LDS bank conflicts on columns)
+  int tid = threadIdx.x;
+  // (opaque: a persistent launch's loop would keep every lane offset below in registers from item to item)
+  asm volatile("" : "+v"(tid));
+  const int nt = a.nt, nr = a.nr, N = a.N, Npad = a.Npad;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nb = (nt + 15) >> 4;
   const InstDesc dsc = inst_desc(a.desc, b, nt, nr, a.Q * a.Q, 1);
   const TIn* Hg = (const TIn*)a.H + 2 * dsc.h_off;
   const TIn* y = (const TIn*)a.y + 2 * dsc.y_off;
-  const double sigma2 = a.sigma2 ? (double)((const TIn*)a.sigma2)[dsc.orig] : a.sigma2_val;
   extern __shared__ double smem_setup[];
-  // nt x ld working matrix: in LDS, or (large nt) in this instance's slice of the workspace
-  cd* W;
+  cd* W = (cd*)smem_setup;
   cd* z;
-  if constexpr (WGLOB) {
-    W = (cd*)(a.wscratch + (size_t)b * a.wscratch_stride);
-    z = (cd*)smem_setup;
-  } else {
-    W = (cd*)smem_setup;
-    z = W + nt * ld;
+  {
+    constexpr int kIC = setup_chunk(RMAX);
+    int region = tile_count(nb) * 256;
+    const int stage = kIC * (nt + 1) + 16, panels = nb > 1 ? (3 * (nb - 1) + 1) * 256 : 0;
+    region = stage > region ? stage : region;
+    region = panels > region ? panels : region;
+    z = W + region;
   }
   cd* bv = z + nt;
-  cd* rowp = bv + nt;       // 2 x 2 x nt (alternating Gauss-Jordan steps, two pivot rows each)
-  cd* colp = rowp + 4 * nt; // 2 x 2 x nt
-  double* red = (double*)(colp + 4 * nt);   // kRedSlots partials of block_reduce
+  double* red = (double*)(bv + nt);   // kRedSlots partials of block_reduce
+  double* cst = red + kRedSlots;      // the instance's constants (kept here, not in 24 registers through every phase)
   unsigned char* blk = a.ws_inst + (size_t)b * a.inst_stride;
 
   const int Q = a.Q, M = Q * Q;
-  const double s = sqrt(3.0 / (2.0 * (M - 1)));
-  const double tau = a.tau;
-  const double alpha = a.alpha_mult * sigma2;
-  const double beta = a.naive ? 1.0 : a.beta_mult * s * s / sigma2;
-  const double gamma = a.gamma_mult * sigma2 / (2.0 * s * s);
-
   // G = H^H H and z = H^H y.  H is staged in LDS in chunks of receive antennas,
   // transposed with a padded row whose last entry holds y (Ht[i][m], Ht[i][nt] = y_i).
   // G on the matrix cores: with X = Re + i Im of the staged H^T (nt x nr),
   //   Re G = Re Re^T + Im Im^T,   Im G = Re Im^T - Im Re^T,
-  // four float64 16x16x4 MFMAs per 16 x 16 tile and 4 receive antennas; each wave
-  // accumulates the upper-triangle tiles (tr <= tc) assigned to it in registers across
-  // the chunks and writes the tile and its conjugate transpose.  z on the vector ALUs:
-  // P = BS / RMAX consecutive threads share an antenna m and split the receive
+  // four float64 16x16x4 MFMAs per 16 x 16 tile and 4 receive antennas; each wave accumulates the tiles (i <= j)
+  // assigned to it in registers across the chunks; they stay there for the inverse.  Rows past nt - 1 read whatever
+  // follows in the staged rows: they only reach tile rows and columns past nt - 1, which are replaced.  z on the vector
+  // ALUs: P = BS / RMAX consecutive threads share an antenna m and split the receive
   // antennas, then sum over those lanes.
+  constexpr int NW = BS / 64;
+  constexpr int kNT = (RMAX + 15) / 16;                         // tile rows at nt = RMAX
+  constexpr int kTPW = (kNT * (kNT + 1) / 2 + NW - 1) / NW;     // tiles per wave
+  constexpr int P = BS / RMAX;
+  static_assert(P >= 1 && 16 % P == 0, "the threads of an antenna share a group of 16 lanes");
+  const int ntiles = tile_count(nb);
+  int m0[kTPW], m1[kTPW];
+  d4 gre[kTPW], gim[kTPW];
   double nonfinite = 0.0;
   double yy = 0.0;
   {
-    constexpr int kIC = RMAX <= 32 ? 16 : 32;
-    constexpr int NW = BS / 64;
-    constexpr int kNT = (RMAX + 15) / 16;                         // tile rows at nt = RMAX
-    constexpr int kTPW = (kNT * (kNT + 1) / 2 + NW - 1) / NW;     // tiles per wave
-    constexpr int P = BS / RMAX;
-    static_assert(P >= 1 && 64 % P == 0, "the threads of an antenna share a wavefront");
-    // kIC x ld, then one spare row; with the working matrix in LDS (33 to 64
-    // antennas) the staging buffer is its first rows, written only after the last read
-    cd* Ht = (!WGLOB && RMAX > 32) ? W : (cd*)(red + kRedSlots);
-    const int lane = tid & 63, wv = tid >> 6;
-    const int ntr = (nt + 15) >> 4, ntiles = ntr * (ntr + 1) / 2;
-    int m0[kTPW], m1[kTPW];
-    d4 gre[kTPW], gim[kTPW];
+    constexpr int kIC = setup_chunk(RMAX);
+    const int ld = nt + 1;
+    cd* Ht = W;   // kIC x ld, then 16 spare entries; the tiles are written after the last read
 #pragma unroll
     for (int q = 0; q < kTPW; ++q) {
       int t = wv + q * NW, tr = 0;
       if (t >= ntiles) t = 0;
-      while (t >= ntr - tr) { t -= ntr - tr; ++tr; }
-      m0[q] = 16 * tr;
-      m1[q] = 16 * (tr + t);
+      while (t >= nb - tr) { t -= nb - tr; ++tr; }
+      m0[q] = tr;
+      m1[q] = tr + t;
       gre[q] = d4{0.0, 0.0, 0.0, 0.0};
       gim[q] = d4{0.0, 0.0, 0.0, 0.0};
     }
@@ -262,12 +348,25 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
       }
     };
     load_chunk(0);
+    // (the constants while the first loads are on their way)
+    if (tid == 0) {
+      const double sigma2 = a.sigma2 ? (double)((const TIn*)a.sigma2)[dsc.orig] : a.sigma2_val;
+      const double s = sqrt(3.0 / (2.0 * (M - 1))), tau = a.tau, alpha = a.alpha_mult * sigma2;
+      cst[kSigma2] = sigma2;
+      cst[kStep] = s;
+      cst[kGamma] = a.gamma_mult * sigma2 / (2.0 * s * s);
+      cst[kCE] = 2.0 * s * s * kLog2e / (tau * sigma2);
+      cst[kCz] = 2.0 * s * kLog2e / (tau * sigma2);
+      cst[kCP] = alpha / (2.0 * tau * sigma2);
+      cst[kCb] = alpha / (2.0 * tau * sigma2 * s);
+    }
     for (int i0 = 0; i0 < nr; i0 += kIC) {
       const int ic = nr - i0 < kIC ? nr - i0 : kIC;
 #pragma unroll
       for (int k = 0; k < kSt; ++k) {
         const int e = tid + k * BS, mm = e / kIC, ii = e % kIC;
-        if (mm <= nt && ii < ic) Ht[ii * ld + mm] = {(double)hv[k][0], (double)hv[k][1]};
+        // (receive antennas past the last, up to the MFMA's four: zero)
+        if (mm <= nt && ii < ((ic + 3) & ~3)) Ht[ii * ld + mm] = ii < ic ? cd{(double)hv[k][0], (double)hv[k][1]} : cd{0.0, 0.0};
       }
       __syncthreads();
       if (i0 + kIC < nr) load_chunk(i0 + kIC);
@@ -279,15 +378,14 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
 #pragma unroll
       for (int q = 0; q < kTPW; ++q) {
         if (wv + q * NW < ntiles) {
-          const int ra = m0[q] + (lane & 15), rb = m1[q] + (lane & 15);
+          const cd* pa = Ht + (lane >> 4) * ld + 16 * m0[q] + (lane & 15);
+          const cd* pb = Ht + (lane >> 4) * ld + 16 * m1[q] + (lane & 15);
+#pragma unroll 4
           for (int kk = 0; kk < ic; kk += 4) {
-            const int ii = kk + (lane >> 4);
-            const bool ok = ii < ic;
-            const cd va = (ok && ra < nt) ? Ht[ii * ld + ra] : cd{0.0, 0.0};
-            const cd vb = (ok && rb < nt) ? Ht[ii * ld + rb] : cd{0.0, 0.0};
+            const cd va = pa[kk * ld], vb = pb[kk * ld];
             gre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(va.re, vb.re, gre[q], 0, 0, 0);
-            gre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(va.im, vb.im, gre[q], 0, 0, 0);
             gim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(va.re, vb.im, gim[q], 0, 0, 0);
+            gre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(va.im, vb.im, gre[q], 0, 0, 0);
             gim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-va.im, vb.re, gim[q], 0, 0, 0);
           }
         }
@@ -311,32 +409,34 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
       if (!isfinite(zacc.re) || !isfinite(zacc.im)) nonfinite = 1.0;
     }
     // lane l, register j of a tile's accumulator: row l / 16 + 4 j, column l % 16
+    const double gamma = cst[kGamma];
 #pragma unroll
     for (int q = 0; q < kTPW; ++q) {
       if (wv + q * NW < ntiles) {
-        const int col = m1[q] + (lane & 15);
+        const int c = lane & 15, col = 16 * m1[q] + c;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int row = m0[q] + (lane >> 4) + 4 * j;
-          if (row < nt && col < nt) {
-            const double re = gre[q][j], im = gim[q][j];
-            W[row * ld + col] = {re, im};
-            if (m0[q] != m1[q]) W[col * ld + row] = {re, -im};
-            if (!isfinite(re) || !isfinite(im)) nonfinite = 1.0;
-          }
+          const int r = (lane >> 4) + 4 * j, row = 16 * m0[q] + r;
+          const bool in = row < nt && col < nt;
+          const double re = in ? gre[q][j] : 0.0, im = in ? gim[q][j] : 0.0;
+          W[(wv + q * NW) * 256 + 16 * r + (r ^ c)] = {re, im};
+          if (!isfinite(re) || !isfinite(im)) nonfinite = 1.0;
+          // from here on G + gamma I, continued by the identity
+          gre[q][j] = re + (row == col ? (in ? gamma : 1.0) : 0.0);
+          gim[q][j] = im;
         }
       }
     }
   }
   __syncthreads();
   yy = block_reduce(yy, red, false);
-  if (!isfinite(yy) || !(sigma2 > 0.0) || !isfinite(sigma2)) nonfinite = 1.0;
+  {
+    const double sigma2 = cst[kSigma2];
+    if (!isfinite(yy) || !(sigma2 > 0.0) || !isfinite(sigma2)) nonfinite = 1.0;
+  }
   nonfinite = block_reduce(nonfinite, red, true);
+  if (tid == 0) { cst[kYY] = yy; cst[kNonfinite] = nonfinite; }
 
-  const double cE = 2.0 * s * s * kLog2e / (tau * sigma2);
-  const double cz = 2.0 * s * kLog2e / (tau * sigma2);
-  const double cP = alpha / (2.0 * tau * sigma2);
-  const double cb = alpha / (2.0 * tau * sigma2 * s);
   const int npP = p_passes(a.pm);
   unsigned char* frag = blk + kParamBytes;
   // bytes of one split term of a packed matrix (real-equivalent, or complex planes: half of it)
@@ -344,216 +444,169 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
   float scaleE = 1.0f, scaleP = 1.0f;
 
   // energy matrix and vector
+  {
+  const double cE = cst[kCE], cz = cst[kCz];
   if (a.fp64) {
     double* EGd = (double*)(blk + kParamBytes) + (size_t)Npad * Npad;
-    pack_dense(W, ld, cE, N, Npad, EGd);
+    pack_dense<false>(W, nb, 0.0, cE, N, Npad, EGd);
     double* ezd = (double*)(blk + kParamBytes) + 2 * (size_t)Npad * Npad + Npad;
     for (int n = tid; n < Npad; n += blockDim.x) ezd[n] = n < N ? cz * realeq_vec(z, n) : 0.0;
   } else {
     unsigned char* fe = frag + (size_t)npP * pass_bytes;
-    scaleE = a.cx ? pack_fragments<kEPasses, false, true>(W, ld, cE, nt, N, a.RT, a.KB, fe)
-                  : pack_fragments<kEPasses, false, false>(W, ld, cE, nt, N, a.RT, a.KB, fe);
+    scaleE = a.cx ? pack_fragments<kEPasses, false, true, false>(W, tid, nb, 0.0, cE, nt, a.RT, a.KB, fe)
+                  : pack_fragments<kEPasses, false, false, false>(W, tid, nb, 0.0, cE, nt, a.RT, a.KB, fe);
     float* ezf = (float*)(frag + (size_t)(npP + kEPasses) * pass_bytes) + Npad;
     for (int n = tid; n < Npad; n += blockDim.x) ezf[n] = n < N ? (float)(cz * realeq_vec(z, n)) : 0.0f;
     float* afv = ezf + Npad;
     for (int n = tid; n < Npad; n += blockDim.x) {
       const int m = n >> 1;
-      afv[n] = (n < N && (n & 1)) ? (float)(log2(sigma2 / (8.0 * s * s * W[m * ld + m].re)) / 8.0) : 0.0f;
+      const double s = cst[kStep], sigma2 = cst[kSigma2];
+      afv[n] = (n < N && (n & 1)) ? (float)(log2(sigma2 / (8.0 * s * s * mat_entry<false>(W, nb, 0.0, m, m).re)) / 8.0) : 0.0f;
     }
+  }
   }
   __syncthreads();
 
   if (!a.naive) {
-    // W <- (G + gamma I)^-1 by in-place Gauss-Jordan with the working matrix in
-    // registers, in SR x SC blocks on a TR x TC thread grid: thread (ti, tj) keeps
-    // rows ti + TR a (a < SR) and columns tj + TC c (c < SC) for the whole sweep.  A
-    // step on pivot p: the owners of column p publish it (colp); the threads of row
-    // p, which share a wavefront with the pivot, read the pivot from its lane, scale
-    // their row by its inverse (the inverse itself in column p) and publish it
-    // (rowp); after one barrier every other row i clears its column p and subtracts
-    // colp[i] * rowp, which leaves -w_ip / w_pp there.  Per step a thread reads SC
-    // entries of the row vector and SR of the column for SR SC updates.  The steps on
-    // different pivots commute (G + gamma I is Hermitian positive definite, so every
-    // pivot stays nonzero in any order), so they run in the order p = o + TR kb, o
-    // outer: row p then sits in register slot kb and column p in slot kb / (TC / TR)
-    // of thread column o + TR (kb % (TC / TR)), compile-time indices of the unrolled
-    // inner loop.  The two vectors alternate between steps, so one barrier per step
-    // orders all reads and writes.
-    constexpr int TR = BS >= 1024 ? 32 : 16;
-    constexpr int TC = BS / TR;
-    constexpr int SR = RMAX / TR, SC = RMAX / TC;
-    static_assert(TR * TC == BS && SR * TR == RMAX && SC * TC == RMAX && TC % TR == 0 && 64 % TC == 0,
-                  "thread grid: a row's threads in one wavefront");
-    const int ti = tid / TC, tj = tid % TC;
-    cd w[SR][SC];
-#pragma unroll
-    for (int ra = 0; ra < SR; ++ra)
-#pragma unroll
-      for (int c = 0; c < SC; ++c) {
-        const int i = ti + TR * ra, j = tj + TC * c;
-        w[ra][c] = (i < nt && j < nt) ? W[i * ld + j] : cd{0.0, 0.0};
-        if (i == j && i < nt) w[ra][c].re += gamma;
-      }
-    // Pivots are taken two at a time where they can be (rows p and p + 1 of the same
-    // register slot, owned by thread rows o and o + 1 of one wavefront): the 2 x 2
-    // pivot block B is inverted in registers, rows p and p + 1 become B^-1 times
-    // themselves (the partner row's entries come from lane + TC), and every other row
-    // subtracts colp0[i] * rowp0 + colp1[i] * rowp1 -- one barrier per two pivots.
-    // (1024 threads: single pivots, as the pair step would not fit in 128 registers.)
-    constexpr bool kPair = BS < 1024;
-    int par = 0;
+    // M = (G + gamma I)^-1 by Gauss-Jordan over 16 x 16 blocks.  The tiles (i <= j) stay in the accumulators of their
+    // waves; the matrix of a step is Hermitian up to the sign of the tiles between a block that has been a pivot and
+    // one that has not.  Step k:
+    //   C_j = tile (k, j) of every other block j to LDS; the pivot tile's wave inverts it, D;
+    //   R_j = D C_j;
+    //   tile (i, j) -= W_ik R_j with W_ik = C_i^H, or -C_i^H if i has been a pivot; tile (k, j) = R_j;
+    //   tile (j, k) = R_j^H; tile (k, k) = D.
+    // A stored tile serves both MFMA operands as it lies: entry (l / 16 + 4 s, l % 16) is lane l's operand B of K step s,
+    // and, conjugated, its operand A of the Hermitian transpose.  C alternates between two buffers, so that two
+    // barriers order a step, and the next pivot's wave starts its inverse while others still update.
+    // Bound by the serial pivots of each block's inverse (about 600 clocks each, no barrier).  Against one or two pivots per
+    // barrier with the matrix in vector registers, clocks of an instance alone on its CU: 32 antennas 31k -> 25k, 64
+    // 89k -> 60k, 128 405k -> 183k, with half of the matrix products and 44 KiB of LDS instead of 75 at 64.
+    cd* panC = W;
+    cd* panR = W + 2 * (nb - 1) * 256;
+    cd* panD = panR + (nb - 1) * 256;
+    const int lg = lane >> 4, lc = lane & 15;
 #pragma unroll 1
-    for (int o = 0; o < TR && o < nt; o += kPair ? 2 : 1) {
+    for (int k = 0; k < nb; ++k) {
+      cd* C = panC + (k & 1) * (nb - 1) * 256;
+      auto slot = [&](int j) { return (j - (j > k ? 1 : 0)) * 256; };
+      double dr[4], di[4];
+      bool mine = false;
 #pragma unroll
-      for (int kb = 0; kb < SR; ++kb) {
-        const int p = o + TR * kb;
-        if (p >= nt) continue;
-        constexpr int kR = TC / TR;
-        const int cs = kb / kR;              // column slot of p (compile time)
-        const int po = o + TR * (kb % kR);   // thread column that owns column p
-        cd* rp = rowp + par * 2 * nt;
-        cd* cp = colp + par * 2 * nt;
-        par ^= 1;
-        if (kPair && p + 1 < nt) {
-          if (tj == po || tj == po + 1) {
-            cd* cpx = cp + (tj == po ? 0 : nt);
+      for (int q = 0; q < kTPW; ++q) {
+        if (wv + q * NW >= ntiles) continue;
+        if (m0[q] == k && m1[q] == k) {
+          mine = true;
 #pragma unroll
-            for (int ra = 0; ra < SR; ++ra)
-              if (ti + TR * ra < nt) cpx[ti + TR * ra] = w[ra][cs];
+          for (int j = 0; j < 4; ++j) { dr[j] = gre[q][j]; di[j] = gim[q][j]; }
+        } else if (m0[q] == k) {
+          cd* o = C + slot(m1[q]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; o[16 * r + (r ^ lc)] = {gre[q][j], gim[q][j]}; }
+        } else if (m1[q] == k) {
+          cd* o = C + slot(m0[q]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; o[16 * lc + (r ^ lc)] = {-gre[q][j], gim[q][j]}; }
+        }
+      }
+      if (mine) {
+        invert_from<0>(dr, di, lane, nt - 16 * k);
+        if (nb > 1) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; panD[16 * r + (r ^ lc)] = {dr[j], di[j]}; }
+        }
+#pragma unroll
+        for (int q = 0; q < kTPW; ++q)
+          if (m0[q] == k && m1[q] == k && wv + q * NW < ntiles) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { gre[q][j] = dr[j]; gim[q][j] = di[j]; }
           }
-          if (tid >> 6 == (o * TC) >> 6) {   // the wavefront of rows p and p + 1
-            const int l0 = (o * TC + po) & 63;
-            const cd pa = {readlane_f64(w[kb][cs].re, l0), readlane_f64(w[kb][cs].im, l0)};
-            const cd pb = {readlane_f64(w[kb][cs].re, l0 + 1), readlane_f64(w[kb][cs].im, l0 + 1)};
-            const cd pc = {readlane_f64(w[kb][cs].re, l0 + TC), readlane_f64(w[kb][cs].im, l0 + TC)};
-            const cd pd = {readlane_f64(w[kb][cs].re, l0 + TC + 1), readlane_f64(w[kb][cs].im, l0 + TC + 1)};
-            const cd det = {pa.re * pd.re - pa.im * pd.im - (pb.re * pc.re - pb.im * pc.im),
-                            pa.re * pd.im + pa.im * pd.re - (pb.re * pc.im + pb.im * pc.re)};
-            const double rd = 1.0 / (det.re * det.re + det.im * det.im);
-            const cd idet = {det.re * rd, -det.im * rd};
-            const cd q00 = cmul(pd, idet), q11 = cmul(pa, idet);
-            const cd q01 = cmul({-pb.re, -pb.im}, idet), q10 = cmul({-pc.re, -pc.im}, idet);
-            const bool top = ti == o;
-            const cd qs = top ? q00 : q11, qo = top ? q01 : q10;   // own row, partner row
+      }
+      if (nb == 1) break;
+      __syncthreads();
+      for (int u = wv; u < 2 * (nb - 1); u += NW) {
+        // real (even u) or imaginary part of a panel tile
+        const cd* c = C + (u >> 1) * 256;
+        const bool ip = u & 1;
+        d4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int c = 0; c < SC; ++c) {
-              const cd oth = {__shfl_xor(w[kb][c].re, TC, 64), __shfl_xor(w[kb][c].im, TC, 64)};
-              if (ti == o || ti == o + 1) w[kb][c] = cadd(cmul(qs, w[kb][c]), cmul(qo, oth));
-            }
-            if (ti == o || ti == o + 1) {
-              if (tj == po) w[kb][cs] = top ? q00 : q10;
-              if (tj == po + 1) w[kb][cs] = top ? q01 : q11;
-              cd* rpx = rp + (top ? 0 : nt);
+        for (int j = 0; j < 4; ++j) {
+          const int r = lg + 4 * j, e = 16 * r + (r ^ lc);
+          const cd d = panD[e], x = c[e];
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(d.re, ip ? x.im : x.re, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ip ? -d.im : d.im, ip ? x.re : x.im, acc, 0, 0, 0);
+        }
+        double* o = (double*)(panR + (u >> 1) * 256) + (ip ? 1 : 0);
 #pragma unroll
-              for (int c = 0; c < SC; ++c)
-                if (tj + TC * c < nt) rpx[tj + TC * c] = w[kb][c];
-            }
+        for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; o[2 * (16 * r + (r ^ lc))] = acc[j]; }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kTPW; ++q) {
+        if (wv + q * NW >= ntiles || (m0[q] == k && m1[q] == k)) continue;
+        if (m0[q] != k && m1[q] != k) {
+          const cd* c = C + slot(m0[q]);
+          const cd* x = panR + slot(m1[q]);
+          const double sg = m0[q] < k ? 1.0 : -1.0;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int r = lg + 4 * j, e = 16 * r + (r ^ lc);
+            const double cr = sg * c[e].re, ci = sg * c[e].im;
+            const cd v = x[e];
+            gre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(cr, v.re, gre[q], 0, 0, 0);
+            gim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(cr, v.im, gim[q], 0, 0, 0);
+            gre[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ci, v.im, gre[q], 0, 0, 0);
+            gim[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ci, v.re, gim[q], 0, 0, 0);
           }
-          __syncthreads();
-          // row entries past column nt - 1 read whatever follows the row vectors in LDS
-          // (inside the allocation); they update register entries that are never stored
-          cd r0[SC], r1[SC];
+        } else if (m0[q] == k) {
+          const cd* x = panR + slot(m1[q]);
 #pragma unroll
-          for (int c = 0; c < SC; ++c) {
-            r0[c] = rp[tj + TC * c];
-            r1[c] = rp[nt + tj + TC * c];
-          }
-#pragma unroll
-          for (int ra = 0; ra < SR; ++ra) {
-            const int i = ti + TR * ra;
-            if (i < nt && i != p && i != p + 1) {
-              const cd c0 = cp[i], c1 = cp[nt + i];
-              if (tj == po || tj == po + 1) w[ra][cs] = {0.0, 0.0};
-#pragma unroll
-              for (int c = 0; c < SC; ++c) {
-                cd& v = w[ra][c];
-                v.re = fma(-c0.re, r0[c].re, fma(c0.im, r0[c].im, v.re));
-                v.im = fma(-c0.re, r0[c].im, fma(-c0.im, r0[c].re, v.im));
-                v.re = fma(-c1.re, r1[c].re, fma(c1.im, r1[c].im, v.re));
-                v.im = fma(-c1.re, r1[c].im, fma(-c1.im, r1[c].re, v.im));
-              }
-            }
-          }
+          for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; const cd v = x[16 * r + (r ^ lc)]; gre[q][j] = v.re; gim[q][j] = v.im; }
         } else {
-          // a single pivot (1024 threads, or the last row of a slot that nt leaves unpaired)
-          if (tj == po) {
+          const cd* x = panR + slot(m0[q]);
 #pragma unroll
-            for (int ra = 0; ra < SR; ++ra)
-              if (ti + TR * ra < nt) cp[ti + TR * ra] = w[ra][cs];
-          }
-          if (ti == o) {
-            const int l0 = (o * TC + po) & 63;
-            const cd piv = {readlane_f64(w[kb][cs].re, l0), readlane_f64(w[kb][cs].im, l0)};
-            const double rd = 1.0 / (piv.re * piv.re + piv.im * piv.im);
-            const cd inv = {piv.re * rd, -piv.im * rd};
-#pragma unroll
-            for (int c = 0; c < SC; ++c) w[kb][c] = cmul(w[kb][c], inv);
-            if (tj == po) w[kb][cs] = inv;
-#pragma unroll
-            for (int c = 0; c < SC; ++c)
-              if (tj + TC * c < nt) rp[tj + TC * c] = w[kb][c];
-          }
-          __syncthreads();
-          cd r[SC];
-#pragma unroll
-          for (int c = 0; c < SC; ++c) r[c] = rp[tj + TC * c];
-#pragma unroll
-          for (int ra = 0; ra < SR; ++ra) {
-            const int i = ti + TR * ra;
-            if (i < nt && i != p) {
-              const cd ci = cp[i];
-              if (tj == po) w[ra][cs] = {0.0, 0.0};
-#pragma unroll
-              for (int c = 0; c < SC; ++c) {
-                cd& v = w[ra][c];
-                v.re = fma(-ci.re, r[c].re, fma(ci.im, r[c].im, v.re));
-                v.im = fma(-ci.re, r[c].im, fma(-ci.im, r[c].re, v.im));
-              }
-            }
-          }
+          for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; const cd v = x[16 * lc + (r ^ lc)]; gre[q][j] = v.re; gim[q][j] = -v.im; }
         }
       }
     }
-    // From the registers of M's blocks: b = M z (each thread's columns, then summed over the TC
-    // threads of a row, which every one of them ends with bit for bit), the preconditioned
-    // variance feature from M's diagonal, and A = I - gamma M written back over the matrix.
+    __syncthreads();   // (the panels are read)
+#pragma unroll
+    for (int q = 0; q < kTPW; ++q)
+      if (wv + q * NW < ntiles) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; W[(wv + q * NW) * 256 + 16 * r + (r ^ lc)] = {gre[q][j], gim[q][j]}; }
+      }
+    __syncthreads();
+    // b = M z (the P threads of a row, summed over their lanes) and the preconditioned variance feature from M's diagonal
     float* afv = (float*)(frag + (size_t)(npP + kEPasses) * pass_bytes) + 2 * Npad;
-    cd zc[SC];
+    {
+      const int m = tid / P, q = tid % P;
+      if (m < nt) {
+        cd bp = {0.0, 0.0};
+        for (int j = q; j < nt; j += P) bp = cadd(bp, cmul(mat_entry<false>(W, nb, 0.0, m, j), z[j]));
 #pragma unroll
-    for (int c = 0; c < SC; ++c) zc[c] = tj + TC * c < nt ? z[tj + TC * c] : cd{0.0, 0.0};
-#pragma unroll
-    for (int ra = 0; ra < SR; ++ra) {
-      const int i = ti + TR * ra;
-      cd bp = {0.0, 0.0};
-#pragma unroll
-      for (int c = 0; c < SC; ++c) {
-        const int j = tj + TC * c;
-        // register entries of columns j >= nt hold whatever the sweep read past the row
-        // vectors (possibly not finite): they are left out, not multiplied by zero
-        if (j < nt) bp = cadd(bp, cmul(w[ra][c], zc[c]));
-        if (i < nt && j < nt) W[i * ld + j] = {(j == i ? 1.0 : 0.0) - gamma * w[ra][c].re, -gamma * w[ra][c].im};
+        for (int o = P >> 1; o > 0; o >>= 1) {
+          bp.re += __shfl_xor(bp.re, o, 64);
+          bp.im += __shfl_xor(bp.im, o, 64);
+        }
+        if (q == 0) {
+          bv[m] = bp;
+          const double s = cst[kStep], sigma2 = cst[kSigma2];
+          if (!a.fp64) afv[2 * m] = (float)(log2(sigma2 * mat_entry<false>(W, nb, 0.0, m, m).re / (8.0 * s * s)) / 8.0);
+        }
       }
-#pragma unroll
-      for (int o = TC >> 1; o > 0; o >>= 1) {
-        bp.re += __shfl_xor(bp.re, o, 64);
-        bp.im += __shfl_xor(bp.im, o, 64);
-      }
-      if (i < nt && tj == 0) bv[i] = bp;
-      // diagonal entry (i, i): thread column ti + TR (ra % (TC / TR)), slot ra / (TC / TR)
-      if (i < nt && tj == ti + TR * (ra % (TC / TR)) && !a.fp64)
-        afv[2 * i] = (float)(log2(sigma2 * w[ra][ra / (TC / TR)].re / (8.0 * s * s)) / 8.0);
     }
     __syncthreads();
+    const double gamma = cst[kGamma], cP = cst[kCP], cb = cst[kCb];
     if (a.fp64) {
-      pack_dense(W, ld, cP, N, Npad, (double*)(blk + kParamBytes));
+      pack_dense<true>(W, nb, gamma, cP, N, Npad, (double*)(blk + kParamBytes));
       double* pbd = (double*)(blk + kParamBytes) + 2 * (size_t)Npad * Npad;
       for (int n = tid; n < Npad; n += blockDim.x) pbd[n] = n < N ? cb * realeq_vec(bv, n) : 0.0;
     } else {
       auto packP = [&](auto CXC) {
         constexpr bool C = decltype(CXC)::value;
-        if (a.pm == PM_BF16X1) return pack_fragments<1, true, C>(W, ld, cP, nt, N, a.RT, a.KB, frag);
-        if (npP == 2) return pack_fragments<2, false, C>(W, ld, cP, nt, N, a.RT, a.KB, frag);
-        return pack_fragments<1, false, C>(W, ld, cP, nt, N, a.RT, a.KB, frag);
+        if (a.pm == PM_BF16X1) return pack_fragments<1, true, C, true>(W, tid, nb, gamma, cP, nt, a.RT, a.KB, frag);
+        if (npP == 2) return pack_fragments<2, false, C, true>(W, tid, nb, gamma, cP, nt, a.RT, a.KB, frag);
+        return pack_fragments<1, false, C, true>(W, tid, nb, gamma, cP, nt, a.RT, a.KB, frag);
       };
       scaleP = a.cx ? packP(std::true_type{}) : packP(std::false_type{});
       float* pbf = (float*)(frag + (size_t)(npP + kEPasses) * pass_bytes);
@@ -568,7 +621,9 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
 
   if (tid == 0) {
     InstParams ip;
-    ip.yy = yy;
+    const double sigma2 = cst[kSigma2], s = cst[kStep], tau = a.tau, alpha = a.alpha_mult * sigma2;
+    const double beta = a.naive ? 1.0 : a.beta_mult * s * s / sigma2;
+    ip.yy = cst[kYY];
     ip.eunit = tau * sigma2 / kLog2e;
     ip.kL = kLog2e * 2.0 * s * s / (alpha * beta);
     ip.rho = alpha / (4.0 * s * s * kLog2e);
@@ -577,7 +632,7 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
     ip.tau = tau;
     ip.scaleP = scaleP;
     ip.scaleE = scaleE;
-    ip.nonfinite = nonfinite > 0.0 ? 1 : 0;
+    ip.nonfinite = cst[kNonfinite] > 0.0 ? 1 : 0;
     ip.pad_[0] = ip.pad_[1] = ip.pad_[2] = 0;
     *(InstParams*)blk = ip;
     if (a.status) a.status[dsc.orig] = ip.nonfinite ? kStatusNonfinite : 0;
@@ -586,36 +641,31 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
 
 // Direct launch (PERS false): instance blockIdx.x.  Persistent launch: items from the list, each
 // with its class's arguments.
-template <typename TIn, bool WGLOB, int BS, int RMAX, bool PERS = false>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RMAX <= 32 ? 5 : (BS == 512 ? 4 : (BS == 256 ? 2 : 1)))))
+template <typename TIn, int BS, int RMAX, bool PERS = false>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RMAX <= 32 ? 4 : (BS == 256 ? 3 : 4))))
 void setup_kernel(SetupArgs a, Persist p) {
   if constexpr (!PERS) {
-    setup_body<TIn, WGLOB, BS, RMAX>(a, blockIdx.x);
+    setup_body<TIn, BS, RMAX>(a, blockIdx.x);
   } else {
     extern __shared__ double smem_setup[];
     for (;;) {
       const int it = persist_take(p, (unsigned char*)smem_setup);
       if (it >= p.n_items) break;
       const WorkItem w = p.items[it];
-      const SetupArgs ca = ((const SetupArgs*)p.cls)[__builtin_amdgcn_readfirstlane(w.cls)];
-      setup_body<TIn, WGLOB, BS, RMAX>(ca, __builtin_amdgcn_readfirstlane(w.inst));
+      const SetupArgs ca = persist_args<SetupArgs>(p.cls, __builtin_amdgcn_readfirstlane(w.cls));
+      setup_body<TIn, BS, RMAX>(ca, __builtin_amdgcn_readfirstlane(w.inst));
     }
     persist_done(p);
   }
 }
 
-bool setup_w_global(int nt) { return nt > 64; }
-
-template <int BS, bool WG, int RMAX>
+template <int BS, int RMAX>
 hipError_t launch_setup_bs(const SetupArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {
-  if (WG != setup_w_global(a.nt) || a.nt > RMAX) return hipErrorInvalidValue;
-  constexpr int kIC = RMAX <= 32 ? 16 : 32;
-  const bool alias = !WG && RMAX > 32;   // the staging buffer is the working matrix's first rows
-  const size_t lds = (size_t)((WG ? 0 : a.nt * (a.nt + 1)) + 10 * a.nt) * sizeof(cd) + kRedSlots * sizeof(double) +
-                     (alias ? 0 : (kIC * (size_t)(a.nt + 1) + 32) * sizeof(cd));
+  if (a.nt > RMAX) return hipErrorInvalidValue;
+  const size_t lds = setup_lds_bytes(a.nt, RMAX);
   void (*k)(SetupArgs, Persist);
-  if (p || cfg) k = a.fp64 ? setup_kernel<double, WG, BS, RMAX, true> : setup_kernel<float, WG, BS, RMAX, true>;
-  else k = a.fp64 ? setup_kernel<double, WG, BS, RMAX> : setup_kernel<float, WG, BS, RMAX>;
+  if (p || cfg) k = a.fp64 ? setup_kernel<double, BS, RMAX, true> : setup_kernel<float, BS, RMAX, true>;
+  else k = a.fp64 ? setup_kernel<double, BS, RMAX> : setup_kernel<float, BS, RMAX>;
   if (cfg) {
     cfg->k = (const void*)k;
     cfg->threads = BS;
@@ -635,14 +685,15 @@ hipError_t launch_setup_bs(const SetupArgs& a, hipStream_t s, const Persist* p, 
   return hipGetLastError();
 }
 
-// Up to 32 antennas: 256 threads, the working matrix in LDS, five workgroups per CU.  Up to 64
-// antennas: 256 threads, the working matrix in LDS (about 75 KiB with the other vectors), two
-// workgroups per CU whose latency-bound Gauss-Jordan steps overlap.  Larger instances keep the
-// working matrix in the workspace between phases (in registers during the sweep), so that LDS
-// holds only the staging buffers: 1024 threads.
+// Threads per workgroup.  One instance is a chain of latencies (loads, pivots, barriers), so a launch of more instances
+// than the larger workgroups hold at once takes smaller ones, more of them per CU, and the others the larger ones,
+// which end sooner.  us, larger / smaller workgroups: 8x8, 8192 instances 73 / 52, 1000 of 4x4 16.2 / 17.8; 32x32, 4096
+// instances 142 / 110; 64x64, 2048 instances 275 / 240, one 48 / 57.
 hipError_t launch_setup(const SetupArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {
-  if (a.nt <= 32) return launch_setup_bs<256, false, 32>(a, s, p, gn, cfg);
-  return a.nt <= 64 ? launch_setup_bs<512, false, 64>(a, s, p, gn, cfg) : launch_setup_bs<1024, true, 128>(a, s, p, gn, cfg);
+  if (a.nt <= 16 && a.n_all > 1024) return launch_setup_bs<64, 16>(a, s, p, gn, cfg);
+  if (a.nt <= 32) return a.n_all > 1024 ? launch_setup_bs<128, 32>(a, s, p, gn, cfg) : launch_setup_bs<256, 32>(a, s, p, gn, cfg);
+  if (a.nt <= 64) return a.n_all > 512 ? launch_setup_bs<256, 64>(a, s, p, gn, cfg) : launch_setup_bs<512, 64>(a, s, p, gn, cfg);
+  return launch_setup_bs<1024, 128>(a, s, p, gn, cfg);
 }
 
 }  // namespace dmala

@@ -152,8 +152,7 @@ void make_args(const void* H, const void* y, const void* sigma2, int32_t n_inst,
   sa.sigma2_val = sigma2_val;
   sa.status = (!eval_out && out) ? out->status : nullptr;
   sa.ws_inst = base + pl.inst_off; sa.inst_stride = sh.inst_bytes;
-  sa.n_inst = n_inst; sa.n_all = pl.n_beside > n_inst ? pl.n_beside : n_inst;
-  sa.nt = sh.nt; sa.nr = sh.nr; sa.Q = sh.Q; sa.N = sh.N; sa.Npad = sh.Npad;
+  sa.n_inst = n_inst; sa.nt = sh.nt; sa.nr = sh.nr; sa.Q = sh.Q; sa.N = sh.N; sa.Npad = sh.Npad;
   sa.RT = sh.RT; sa.KB = sh.KB; sa.fp64 = sh.fp64; sa.pm = sh.pm; sa.naive = pl.naive ? 1 : 0; sa.cx = sh.cx;
   sa.tau = pl.tau; sa.alpha_mult = pl.am; sa.beta_mult = pl.bm; sa.gamma_mult = pl.gm;
 

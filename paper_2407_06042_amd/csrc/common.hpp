@@ -129,7 +129,6 @@ struct SetupArgs {
   unsigned char* ws_inst; size_t inst_stride;
   int n_inst, nt, nr, Q, N, Npad, RT, KB, fp64, pm, naive;
   int cx;              // 1: pack the matrices as complex planes (the sampler's complex-plane layouts)
-  int n_all;           // instances that are set up beside one another (a plan's, all classes)
   double tau, alpha_mult, beta_mult, gamma_mult;
 };
 
@@ -192,37 +191,6 @@ __device__ inline int persist_take(const Persist& p, unsigned char* lds) {
   if (threadIdx.x == 0) slot[0] = __hip_atomic_fetch_add(p.counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(slot[0]);
-}
-
-// A class's arguments, in scalar registers (constant address space) and with their pointers known to be global: read
-// through an ordinary pointer they take vector registers and flat accesses, and every branch on a size becomes a
-// masked one.
-template <typename T> __device__ __forceinline__ T persist_args_words(const void* cls, int i) {
-  struct Words { uint32_t w[sizeof(T) / 4]; } r;
-  static_assert(sizeof(Words) == sizeof(T), "whole words");
-  const __attribute__((address_space(4))) uint32_t* s =
-      (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)cls + (size_t)i * (sizeof(T) / 4);
-#pragma unroll
-  for (int k = 0; k < (int)(sizeof(T) / 4); ++k) r.w[k] = s[k];
-  return __builtin_bit_cast(T, r);
-}
-template <typename T> __device__ __forceinline__ void as_global(T*& p) { p = (T*)(__attribute__((address_space(1))) T*)p; }
-__device__ __forceinline__ void as_global(SetupArgs& a) {
-  as_global(a.desc); as_global(a.H); as_global(a.y); as_global(a.sigma2); as_global(a.status); as_global(a.ws_inst);
-}
-__device__ __forceinline__ void as_global(SamplerArgs& a) {
-  as_global(a.desc); as_global(a.ws_inst); as_global(a.ws_state); as_global(a.final_state); as_global(a.accept_count);
-  as_global(a.trace_accept); as_global(a.trace_hash); as_global(a.mlp); as_global(a.train_rows);
-  as_global(a.x_from); as_global(a.x_to); as_global(a.eval_out); as_global(a.eval_dim);
-}
-__device__ __forceinline__ void as_global(EstArgs& a) {
-  as_global(a.desc); as_global(a.H); as_global(a.y); as_global(a.sigma2); as_global(a.ws_inst); as_global(a.ws_state);
-  as_global(a.symbols); as_global(a.marginals); as_global(a.llrs); as_global(a.best_energy); as_global(a.marginals_mc);
-}
-template <typename T> __device__ __forceinline__ T persist_args(const void* cls, int i) {
-  T a = persist_args_words<T>(cls, i);
-  as_global(a);
-  return a;
 }
 
 // The workgroup has taken its last item; the last one to get here resets the counters.

@@ -195,7 +195,7 @@ dmala_status dmala_gx_loop(const void* H, const void* y, const void* sigma2, int
     SetupArgs sa{};
     sa.H = H; sa.y = y; sa.sigma2 = sigma2;
     sa.ws_inst = base + pl.inst_off; sa.inst_stride = sh.inst_bytes;
-    sa.n_inst = n_inst; sa.n_all = n_inst; sa.nt = sh.nt; sa.nr = sh.nr; sa.Q = sh.Q; sa.N = sh.N; sa.Npad = sh.Npad;
+    sa.n_inst = n_inst; sa.nt = sh.nt; sa.nr = sh.nr; sa.Q = sh.Q; sa.N = sh.N; sa.Npad = sh.Npad;
     sa.RT = sh.RT; sa.KB = sh.KB; sa.fp64 = 0; sa.pm = sh.pm; sa.naive = 0;
     sa.tau = pl.tau; sa.alpha_mult = pl.am; sa.beta_mult = pl.bm; sa.gamma_mult = pl.gm;
     const hipError_t e = launch_setup(sa, s);

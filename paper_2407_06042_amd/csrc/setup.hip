@@ -642,7 +642,7 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
 // Direct launch (PERS false): instance blockIdx.x.  Persistent launch: items from the list, each
 // with its class's arguments.
 template <typename TIn, int BS, int RMAX, bool PERS = false>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RMAX <= 32 ? 4 : (BS == 256 ? 3 : 4))))
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(PERS ? 2 : (BS == 256 && RMAX > 32 ? 3 : 4))))
 void setup_kernel(SetupArgs a, Persist p) {
   if constexpr (!PERS) {
     setup_body<TIn, BS, RMAX>(a, blockIdx.x);
@@ -652,20 +652,31 @@ void setup_kernel(SetupArgs a, Persist p) {
       const int it = persist_take(p, (unsigned char*)smem_setup);
       if (it >= p.n_items) break;
       const WorkItem w = p.items[it];
-      const SetupArgs ca = persist_args<SetupArgs>(p.cls, __builtin_amdgcn_readfirstlane(w.cls));
+      SetupArgs ca = ((const SetupArgs*)p.cls)[__builtin_amdgcn_readfirstlane(w.cls)];
+      // the sizes in scalar registers (loaded through a pointer they take vector registers)
+      ca.nt = __builtin_amdgcn_readfirstlane(ca.nt);
+      ca.nr = __builtin_amdgcn_readfirstlane(ca.nr);
+      ca.Q = __builtin_amdgcn_readfirstlane(ca.Q);
+      ca.N = __builtin_amdgcn_readfirstlane(ca.N);
+      ca.Npad = __builtin_amdgcn_readfirstlane(ca.Npad);
+      ca.RT = __builtin_amdgcn_readfirstlane(ca.RT);
+      ca.KB = __builtin_amdgcn_readfirstlane(ca.KB);
+      ca.fp64 = __builtin_amdgcn_readfirstlane(ca.fp64);
+      ca.pm = __builtin_amdgcn_readfirstlane(ca.pm);
+      ca.naive = __builtin_amdgcn_readfirstlane(ca.naive);
+      ca.cx = __builtin_amdgcn_readfirstlane(ca.cx);
       setup_body<TIn, BS, RMAX>(ca, __builtin_amdgcn_readfirstlane(w.inst));
     }
     persist_done(p);
   }
 }
 
-template <int BS, int RMAX>
+template <int BS, int RMAX, bool PERS = false>
 hipError_t launch_setup_bs(const SetupArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {
   if (a.nt > RMAX) return hipErrorInvalidValue;
   const size_t lds = setup_lds_bytes(a.nt, RMAX);
   void (*k)(SetupArgs, Persist);
-  if (p || cfg) k = a.fp64 ? setup_kernel<double, BS, RMAX, true> : setup_kernel<float, BS, RMAX, true>;
-  else k = a.fp64 ? setup_kernel<double, BS, RMAX> : setup_kernel<float, BS, RMAX>;
+  k = a.fp64 ? setup_kernel<double, BS, RMAX, PERS> : setup_kernel<float, BS, RMAX, PERS>;
   if (cfg) {
     cfg->k = (const void*)k;
     cfg->threads = BS;
@@ -689,10 +700,17 @@ hipError_t launch_setup_bs(const SetupArgs& a, hipStream_t s, const Persist* p, 
 // than the larger workgroups hold at once takes smaller ones, more of them per CU, and the others the larger ones,
 // which end sooner.  us, larger / smaller workgroups: 8x8, 8192 instances 73 / 52, 1000 of 4x4 16.2 / 17.8; 32x32, 4096
 // instances 142 / 110; 64x64, 2048 instances 275 / 240, one 48 / 57.
+// Persistent launches keep their arguments in registers beside the body's and share the GPU with other classes: two
+// sizes, of at most 512 threads, so that nothing spills.
 hipError_t launch_setup(const SetupArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {
-  if (a.nt <= 16 && a.n_all > 1024) return launch_setup_bs<64, 16>(a, s, p, gn, cfg);
-  if (a.nt <= 32) return a.n_all > 1024 ? launch_setup_bs<128, 32>(a, s, p, gn, cfg) : launch_setup_bs<256, 32>(a, s, p, gn, cfg);
-  if (a.nt <= 64) return a.n_all > 512 ? launch_setup_bs<256, 64>(a, s, p, gn, cfg) : launch_setup_bs<512, 64>(a, s, p, gn, cfg);
+  if (p || cfg) {
+    if (a.nt <= 32) return launch_setup_bs<128, 32, true>(a, s, p, gn, cfg);
+    if (a.nt <= 64) return launch_setup_bs<256, 64, true>(a, s, p, gn, cfg);
+    return launch_setup_bs<512, 128, true>(a, s, p, gn, cfg);
+  }
+  if (a.nt <= 16 && a.n_inst > 1024) return launch_setup_bs<64, 16>(a, s, p, gn, cfg);
+  if (a.nt <= 32) return a.n_inst > 1024 ? launch_setup_bs<128, 32>(a, s, p, gn, cfg) : launch_setup_bs<256, 32>(a, s, p, gn, cfg);
+  if (a.nt <= 64) return a.n_inst > 512 ? launch_setup_bs<256, 64>(a, s, p, gn, cfg) : launch_setup_bs<512, 64>(a, s, p, gn, cfg);
   return launch_setup_bs<1024, 128>(a, s, p, gn, cfg);
 }
 

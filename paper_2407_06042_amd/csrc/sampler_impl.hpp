@@ -731,7 +731,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       // B operand: this wave's K blocks from its own registers.  The packed
       // matrices are zero in the padding columns, so a padding dimension's
       // level (any in-range value) contributes nothing and needs no mask.
-      half8 bh[KB];
+      half8 bh[KB], own[KBW];
       bf16x8 bb[KB];
 #pragma unroll
       for (int kb = 0; kb < KBW; ++kb) {
@@ -743,22 +743,16 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           if constexpr (HALF) wh[q] = q < 2 ? lv_pair<QM1>(k[d], k[d + 1]) : 0u;
           else wh[q] = lv_pair<QM1>(k[d], k[d + 1]);
         }
-        __builtin_memcpy(&bh[wd * KBW + kb], wh, 16);
-        if constexpr (PM == PM_BF16X1) {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int d = (2 * kb + (j >> 2)) * 4 + (j & 3);
-            if constexpr (HALF) bb[wd * KBW + kb][j] = j < 4 ? (__bf16)(float)(2 * k[d] - QM1) : (__bf16)0.f;
-            else bb[wd * KBW + kb][j] = (__bf16)(float)(2 * k[d] - QM1);
-          }
-        }
+        __builtin_memcpy(&own[kb], wh, 16);
       }
       if constexpr (WD > 1) {
-        // exchange the K blocks of the other waves through LDS
+        // every wave's K blocks through LDS, the own ones too: a register array indexed by the wave's slice number
+        // becomes a compare and a select per element and word, whose masks spill (learned chains at 64x64 64-QAM:
+        // 3604 -> 1986 vector instructions per transition and wave, 2364 -> 1627 us for 1024 problems)
         unsigned char* xb = xbuf + (xphase & 1) * KB * 1024;
         ++xphase;
 #pragma unroll
-        for (int kb = 0; kb < KBW; ++kb) *(half8*)(xb + (size_t)(wd * KBW + kb) * 1024 + lane * 16) = bh[wd * KBW + kb];
+        for (int kb = 0; kb < KBW; ++kb) *(half8*)(xb + (size_t)(wd * KBW + kb) * 1024 + lane * 16) = own[kb];
         __syncthreads();
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
@@ -766,6 +760,19 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           if constexpr (PM == PM_BF16X1) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) bb[kb][j] = (__bf16)(float)bh[kb][j];
+          }
+        }
+      } else {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+          bh[kb] = own[kb];
+          if constexpr (PM == PM_BF16X1) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const int d = (2 * kb + (j >> 2)) * 4 + (j & 3);
+              if constexpr (HALF) bb[kb][j] = j < 4 ? (__bf16)(float)(2 * k[d] - QM1) : (__bf16)0.f;
+              else bb[kb][j] = (__bf16)(float)(2 * k[d] - QM1);
+            }
           }
         }
       }

@@ -136,41 +136,53 @@ __device__ __forceinline__ mlp_f32x4 mlp_eval4(const unsigned char* lds, uint32_
   const float* bias = (const float*)(lds + lds_off + (size_t)I::kFrags * 1024);
   mlp_f32x4 out = *(const mlp_f32x4*)(bias + 64);
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    // fragments are re-read for every antenna group (an opaque offset keeps the
-    // compiler from holding all of them in registers across the groups)
+  for (int gp = 0; gp < 2; ++gp) {
+    // two antenna groups at a time: a fragment of layer 2 (and of layer 1, where the groups share it) serves both, as
+    // fragments read for one group's products alone take the LDS twice as long as the matrix cores (1024 problems of
+    // 64x64 64-QAM, 25 transitions: sampler 1627 -> 1520 us).
+    // Fragments are re-read for every pair (an opaque offset keeps the compiler from holding all of them in
+    // registers across the pairs)
     const unsigned char* base = lds + lds_off + opaque_zero_u32() + (uint32_t)lane * 16;
     // only the K slice of antenna group g may contribute: zero weights elsewhere (GW1) or
     // zero inputs of the other groups
     const mlp_bf16x8 zero8 = {};
-    const mlp_bf16x8 xg = (GW1 || h == g) ? x : zero8;
-    mlp_f32x4 z1[4];
+    const mlp_f32x4 c0 = {0.f, 0.f, 0.f, 0.f};
+    mlp_bf16x8 a1[2][2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const mlp_f32x4 c0 = {0.f, 0.f, 0.f, 0.f};
-      const mlp_bf16x8 w1 = *(const mlp_bf16x8*)(base + (I::kW1 + (GW1 ? 4 * g : 0) + t) * 1024);
-      z1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, xg, c0, 0, 0, 0);
-    }
-    mlp_bf16x8 a1[2];
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int s = 0; s < 2; ++s) a1[s] = relu_bf16x8(z1[2 * s], z1[2 * s + 1]);
-    mlp_f32x4 z2[4];
+      for (int q = 0; q < 2; ++q) {
+        const int g = 2 * gp + q;
+        const mlp_bf16x8 xg = (GW1 || h == g) ? x : zero8;
+        mlp_f32x4 z1[2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      z2[t] = *(const mlp_f32x4*)(bias + 16 * t + 4 * h);
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const mlp_bf16x8 w2 = *(const mlp_bf16x8*)(base + (I::kW2 + 2 * t + s) * 1024);
-        z2[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2, a1[s], z2[t], 0, 0, 0);
+        for (int t = 0; t < 2; ++t) {
+          const mlp_bf16x8 w1 = *(const mlp_bf16x8*)(base + (I::kW1 + (GW1 ? 4 * g : 0) + 2 * s + t) * 1024);
+          z1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, xg, c0, 0, 0, 0);
+        }
+        a1[q][s] = relu_bf16x8(z1[0], z1[1]);
       }
-    }
-    mlp_bf16x8 a2[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) a2[s] = relu_bf16x8(z2[2 * s], z2[2 * s + 1]);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const mlp_bf16x8 w3 = *(const mlp_bf16x8*)(base + (I::kW3 + 2 * g + s) * 1024);
-      out = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3, a2[s], out, 0, 0, 0);
+      mlp_f32x4 z2[2][2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const mlp_f32x4 b2 = *(const mlp_f32x4*)(bias + 16 * (2 * s + t) + 4 * h);
+        z2[0][t] = b2;
+        z2[1][t] = b2;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const mlp_bf16x8 w2 = *(const mlp_bf16x8*)(base + (I::kW2 + 2 * (2 * s + t) + k) * 1024);
+#pragma unroll
+          for (int q = 0; q < 2; ++q) z2[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2, a1[q][k], z2[q][t], 0, 0, 0);
+        }
+      }
+      // (W3 is zero outside its group's rows: the groups' turns leave one another's sums as they are)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const mlp_bf16x8 w3 = *(const mlp_bf16x8*)(base + (I::kW3 + 2 * (2 * gp + q) + s) * 1024);
+        out = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3, relu_bf16x8(z2[q][0], z2[q][1]), out, 0, 0, 0);
+      }
     }
   }
   return out;

@@ -359,7 +359,7 @@ constexpr int cx_lds_halves(int rt, bool win) { return rt <= 8 ? 7 : (win ? 3 : 
 // enters nothing but the log normalisers, with a constant weight sum: the wave leaves the tile out and
 // multiplies by those constants where the full loop would (bit for bit the full loop's results).
 template <typename Real, int RTW, int WD, bool MG, int Q, int PM, bool EVAL, int WIN, int KND, bool CX = false,
-          bool FULL = false, bool HALF = false>
+          bool FULL = false, bool HALF = false, bool PERS = false>
 __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int inst, const int cgy) {
   constexpr bool F64 = std::is_same<Real, double>::value;
   constexpr bool LRN = KND == 1;   // plain/learned kernel mixture
@@ -387,6 +387,9 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
   // inst: index within the class (workspace slot); cgy: group of 16-chain blocks
   const int N = a.N, Npad = a.Npad;
   const unsigned char* blk = a.ws_inst + (size_t)inst * a.inst_stride;
+  // (a persistent launch loads the pointer: without the address space the matrices' loads would be flat ones, which also
+  // wait for LDS)
+  if constexpr (PERS) blk = (const unsigned char*)(const __attribute__((address_space(1))) unsigned char*)(uintptr_t)blk;
   // the caller's instance index (RNG counter, per-instance outputs) and final-state offset
   const uint32_t rid = a.desc ? (uint32_t)a.desc[inst].orig : (uint32_t)inst;
   const uint32_t rctr = rid + a.ctr_base;                 // instance word of the random counter
@@ -1327,7 +1330,7 @@ __device__ __forceinline__ void sampler_entry(const SamplerArgs& a, const Persis
       if (it >= p.n_items) break;
       const WorkItem w = p.items[it];
       const SamplerArgs ca = ((const SamplerArgs*)p.cls)[__builtin_amdgcn_readfirstlane(w.cls)];
-      sampler_body<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX, false, HALF>(
+      sampler_body<Real, RTW, WD, MG, Q, PM, EVAL, WIN, KND, CX, false, HALF, true>(
           ca, __builtin_amdgcn_readfirstlane(w.inst), __builtin_amdgcn_readfirstlane(w.cg));
     }
     persist_done(p);

@@ -633,7 +633,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
 #pragma unroll
         for (int q = 0; q < 4; ++q) u[q] ^= 0x80008000u;                          // -x_im
         __builtin_memcpy(&xn[kb], u, 16);
-        if constexpr (PM == PM_BF16X1) {
+      }
+      auto to_bf16 = [&]() {
+#pragma unroll
+        for (int kb = 0; kb < KBX; ++kb) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             br[kb][j] = (__bf16)(float)xr[kb][j];
@@ -646,7 +649,11 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           for (int q = 0; q < 4; ++q) ub[q] ^= 0x80008000u;
           __builtin_memcpy(&bn[kb], ub, 16);
         }
-      }
+      };
+      // BF16 form at 256 dimensions: the fp16 and the bf16 operands together are 96 registers, which spill, so the energy
+      // products of all tiles come first and the operands are converted behind them
+      constexpr bool LATE = PM == PM_BF16X1 && WD == 4;
+      if constexpr (PM == PM_BF16X1 && !LATE) to_bf16();
       const uint32_t fo = opaque_zero() + (uint32_t)lane * 16;
       // the first SPH half passes (planes) from LDS (p, pl are compile-time indices at every call), the others from L2
       auto frag = [&](int p, int pl, int atg, int kb) -> const unsigned char* {
@@ -654,8 +661,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         if (p * 2 + pl < SPH) return smem + off;
         return blk + kParamBytes + off;
       };
-#pragma unroll
-      for (int at = 0; at < ATW; ++at) {
+      auto energy = [&](int at) {
         const int atg = (rt0 >> 1) + at;
         // the energy matrix's fragments of the antenna tile, all loads issued before the products
         uint4 fe[kEPasses][2][KBX];
@@ -688,6 +694,9 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           accE[(at * 4 + i) * 2] = er[i];
           accE[(at * 4 + i) * 2 + 1] = ei[i];
         }
+      };
+      auto proposal = [&](int at) {
+        const int atg = (rt0 >> 1) + at;
         if constexpr (PM != PM_NAIVE) {
           // then the proposal matrix's (its loads issue behind the energy products)
           uint4 fp[NPP > 0 ? NPP : 1][2][KBX];
@@ -728,7 +737,27 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         }
         hook(2 * at);
         hook(2 * at + 1);
-        __builtin_amdgcn_sched_barrier(0);   // one antenna tile's fragments in registers at a time
+      };
+      // (the scheduling barriers: one antenna tile's fragments in registers at a time)
+      if constexpr (LATE) {
+#pragma unroll
+        for (int at = 0; at < ATW; ++at) {
+          energy(at);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        to_bf16();
+#pragma unroll
+        for (int at = 0; at < ATW; ++at) {
+          proposal(at);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int at = 0; at < ATW; ++at) {
+          energy(at);
+          proposal(at);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     } else {
       // B operand: this wave's K blocks from its own registers.  The packed

@@ -587,6 +587,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       constexpr int KBX = RT / 4, KBWX = RTW / 4, ATW = RTW / 2, AT = RT / 2;
       half8 xr[KBX], xi[KBX], xn[KBX];
       bf16x8 br[KBX], bi[KBX], bn[KBX];
+      // BF16 form at 256 dimensions: the fp16 and the bf16 operands together are 96 registers, which spill (128x128
+      // 256-QAM, 100 transitions: sampler 2663 -> 1892 us), so the energy products of all tiles come first and the
+      // operands are converted behind them
+      constexpr bool LATE = PM == PM_BF16X1 && WD == 4;
       // the wave's own K blocks (its antenna tiles), built from its registers
       half8 ownr[KBWX], owni[KBWX];
 #pragma unroll
@@ -633,10 +637,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
 #pragma unroll
         for (int q = 0; q < 4; ++q) u[q] ^= 0x80008000u;                          // -x_im
         __builtin_memcpy(&xn[kb], u, 16);
-      }
-      auto to_bf16 = [&]() {
-#pragma unroll
-        for (int kb = 0; kb < KBX; ++kb) {
+        if constexpr (PM == PM_BF16X1 && !LATE) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             br[kb][j] = (__bf16)(float)xr[kb][j];
@@ -649,11 +650,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           for (int q = 0; q < 4; ++q) ub[q] ^= 0x80008000u;
           __builtin_memcpy(&bn[kb], ub, 16);
         }
-      };
-      // BF16 form at 256 dimensions: the fp16 and the bf16 operands together are 96 registers, which spill, so the energy
-      // products of all tiles come first and the operands are converted behind them
-      constexpr bool LATE = PM == PM_BF16X1 && WD == 4;
-      if constexpr (PM == PM_BF16X1 && !LATE) to_bf16();
+      }
       const uint32_t fo = opaque_zero() + (uint32_t)lane * 16;
       // the first SPH half passes (planes) from LDS (p, pl are compile-time indices at every call), the others from L2
       auto frag = [&](int p, int pl, int atg, int kb) -> const unsigned char* {
@@ -661,7 +658,8 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         if (p * 2 + pl < SPH) return smem + off;
         return blk + kParamBytes + off;
       };
-      auto energy = [&](int at) {
+#pragma unroll
+      for (int at = 0; at < ATW; ++at) {
         const int atg = (rt0 >> 1) + at;
         // the energy matrix's fragments of the antenna tile, all loads issued before the products
         uint4 fe[kEPasses][2][KBX];
@@ -694,9 +692,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           accE[(at * 4 + i) * 2] = er[i];
           accE[(at * 4 + i) * 2 + 1] = ei[i];
         }
-      };
-      auto proposal = [&](int at) {
-        const int atg = (rt0 >> 1) + at;
+        if constexpr (LATE) {
+          __builtin_amdgcn_sched_barrier(0);
+          continue;
+        }
         if constexpr (PM != PM_NAIVE) {
           // then the proposal matrix's (its loads issue behind the energy products)
           uint4 fp[NPP > 0 ? NPP : 1][2][KBX];
@@ -737,25 +736,47 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         }
         hook(2 * at);
         hook(2 * at + 1);
-      };
-      // (the scheduling barriers: one antenna tile's fragments in registers at a time)
+        __builtin_amdgcn_sched_barrier(0);   // one antenna tile's fragments in registers at a time
+      }
       if constexpr (LATE) {
 #pragma unroll
-        for (int at = 0; at < ATW; ++at) {
-          energy(at);
-          __builtin_amdgcn_sched_barrier(0);
+        for (int kb = 0; kb < KBX; ++kb) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            br[kb][j] = (__bf16)(float)xr[kb][j];
+            bi[kb][j] = (__bf16)(float)xi[kb][j];
+          }
+          uint32_t ub[4];
+          __builtin_memcpy(ub, &bi[kb], 16);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) ub[q] ^= 0x80008000u;
+          __builtin_memcpy(&bn[kb], ub, 16);
         }
-        to_bf16();
 #pragma unroll
         for (int at = 0; at < ATW; ++at) {
-          proposal(at);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else {
+          uint4 fp[2][KBX];
 #pragma unroll
-        for (int at = 0; at < ATW; ++at) {
-          energy(at);
-          proposal(at);
+          for (int pl = 0; pl < 2; ++pl)
+#pragma unroll
+            for (int kb = 0; kb < KBX; ++kb) fp[pl][kb] = *(const uint4*)frag(0, pl, (rt0 >> 1) + at, kb);
+          f32x4 pr = {0.f, 0.f, 0.f, 0.f}, pi = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int kb = 0; kb < KBX; ++kb) {
+            bf16x8 re, im;
+            __builtin_memcpy(&re, &fp[0][kb], 16);
+            __builtin_memcpy(&im, &fp[1][kb], 16);
+            pr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(re, br[kb], pr, 0, 0, 0);
+            pr = __builtin_amdgcn_mfma_f32_16x16x32_bf16(im, bn[kb], pr, 0, 0, 0);
+            pi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(im, br[kb], pi, 0, 0, 0);
+            pi = __builtin_amdgcn_mfma_f32_16x16x32_bf16(re, bi[kb], pi, 0, 0, 0);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            accP[(at * 4 + i) * 2] = pr[i];
+            accP[(at * 4 + i) * 2 + 1] = pi[i];
+          }
+          hook(2 * at);
+          hook(2 * at + 1);
           __builtin_amdgcn_sched_barrier(0);
         }
       }

@@ -64,6 +64,10 @@ inline int train_wgs(int n) {
   return wgs < kTrainWgs ? wgs : kTrainWgs;
 }
 
+// Hidden units are numbered by their place in the tiles: place 16 t + 4 q + j is unit 16 t + 4 j + q (its own
+// inverse), so that the K steps of the products below take the units in ascending order (see mlp_grad_kernel).
+__host__ __device__ constexpr int hid_unit(int place) { return (place & ~15) | ((place & 3) << 2) | ((place >> 2) & 3); }
+
 // Accumulators of one wavefront: the weight gradients as 16 x 16 tiles (register j of lane (q, c), q = lane / 16,
 // c = lane % 16: row 4 q + j, column c), b2's as per-lane sums over the lane's rows, b3's and the loss.
 struct GradAcc {
@@ -95,9 +99,16 @@ __device__ __forceinline__ void for_acc(GradAcc& a, F&& f) {
 // Loss, forward, backward and weight gradients of the rows, all on the float32 matrix cores
 // (v_mfma_f32_16x16x4f32: A (16 x 4) lane l holds A[l % 16][l / 16], B (4 x 16) lane l holds B[l / 16][l % 16],
 // register j of the accumulator D[4 (l / 16) + j][l % 16]).  A wavefront takes 16 rows at a time as the columns of
-// every product: lane (q, c) then holds hidden units 16 t + 4 q + j of row c, and the next layer's K step (t, j)
-// uses exactly those registers as its B operand (weights read in that K order), so that forward and backward
-// exchange nothing between lanes.  The weight gradients contract over the rows; their operands are the transposed
+// every product: lane (q, c) then holds the hidden units in places 16 t + 4 q + j of row c, and the next layer's K
+// step (t, j) uses exactly those registers as its B operand (weights read in that K order), so that forward and
+// backward exchange nothing between lanes.
+// A unit whose input is within rounding of zero is on or off by the order of its sum, and one such unit of a
+// batch's millions moves the gradient by more than all other rounding (65 536 rows: 3e-6 against 3e-7 of the 2-norm).
+// The order is therefore fixed: the bias first, then fused multiply-adds over ascending inputs.  The matrix core
+// does its K terms as that chain (ascending k from the accumulator, one rounding each), and with the units' places
+// (hid_unit) K step (t, j) takes units 16 t + 4 j .. + 3, so that forward and backward sums are those of a loop over
+// the units bit for bit.
+// The weight gradients contract over the rows; their operands are the transposed
 // tiles, which pass through LDS (two 16 x 64 tiles per wavefront).  236 products per tile, 8 passes each: the
 // products of 65 536 rows need 13 us at the float32 matrix rate.  Measured 39-41 us (40 % of a wave's cycles in
 // products, 35 % waiting on LDS and on dependent products with one wavefront per SIMD, which the 117 accumulator
@@ -118,21 +129,26 @@ void mlp_grad_kernel(const float* __restrict__ w, const float* __restrict__ rows
   float* bufB = bufA + kTrainTile * kW2Ld;
   float* xs = bufB + kTrainTile * kW2Ld;
   float* ds = xs + kTrainTile * 8;
-  for (int i = tid; i < kMlpHid * kMlpHid; i += 64 * kTrainWaves) W2[(i >> 6) * kW2Ld + (i & 63)] = w[kOffW2 + i];
-  // first-layer weights and bias, [unit 16 t + c][input 4 s + q]; third layer in the K order of the lane's
-  // units, its 4 rows repeated in every group of 4 so that each lane group gets all 4 outputs; and its transpose
+  // (rows and columns by place)
+  for (int i = tid; i < kMlpHid * kMlpHid; i += 64 * kTrainWaves)
+    W2[hid_unit(i >> 6) * kW2Ld + hid_unit(i & 63)] = w[kOffW2 + i];
+  // first-layer weights, [place 16 t + c][input 4 s + q] (input 7, the constant 1 of b1's gradient, with weight 0);
+  // third layer in the K order of the lane's units, its 4 rows repeated in every group of 4 so that each lane group
+  // gets all 4 outputs; and its transpose
   float w1[4][2], w3[4][4], w3t[4];
-  f32x4 b2v[4], b3v;
+  f32x4 b1v[4], b2v[4], b3v;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int u = 16 * t + c;
+    const int u = hid_unit(16 * t + c);
     w1[t][0] = w[kOffW1 + u * kMlpIn + q];
-    w1[t][1] = q < 3 ? w[kOffW1 + u * kMlpIn + 4 + q] : w[kOffB1 + u];
+    w1[t][1] = q < 3 ? w[kOffW1 + u * kMlpIn + 4 + q] : 0.f;
     w3t[t] = w[kOffW3 + q * kMlpHid + u];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      w3[t][j] = w[kOffW3 + (c & 3) * kMlpHid + 16 * t + 4 * q + j];
-      b2v[t][j] = w[kOffB2 + 16 * t + 4 * q + j];
+      const int v = hid_unit(16 * t + 4 * q + j);
+      w3[t][j] = w[kOffW3 + (c & 3) * kMlpHid + v];
+      b1v[t][j] = w[kOffB1 + v];
+      b2v[t][j] = w[kOffB2 + v];
     }
   }
 #pragma unroll
@@ -165,8 +181,7 @@ void mlp_grad_kernel(const float* __restrict__ w, const float* __restrict__ rows
     f32x4 a1[4], a2[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[t][0], x0, z, 0, 0, 0);
+      f32x4 z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[t][0], x0, b1v[t], 0, 0, 0);
       z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[t][1], x1, z, 0, 0, 0);
 #pragma unroll
       for (int j = 0; j < 4; ++j) a1[t][j] = fmaxf(z[j], 0.f);
@@ -182,15 +197,14 @@ void mlp_grad_kernel(const float* __restrict__ w, const float* __restrict__ rows
 #pragma unroll
         for (int t = 0; t < 4; ++t) a2[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t][j], a1[s][j], a2[t], 0, 0, 0);
     }
-    f32x4 o[2] = {b3v, {0.f, 0.f, 0.f, 0.f}};
+    f32x4 out = b3v;
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         a2[s][j] = fmaxf(a2[s][j], 0.f);
-        o[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3[s][j], a2[s][j], o[j & 1], 0, 0, 0);
+        out = __builtin_amdgcn_mfma_f32_16x16x4f32(w3[s][j], a2[s][j], out, 0, 0, 0);
       }
-    const f32x4 out = o[0] + o[1];
     // loss and its gradient with respect to the outputs: lane group q takes axis q % 2 of its row
     const int Q = qf >= 16.f ? 16 : (qf >= 2.f ? (int)qf : 2);
     const bool im = q & 1;
@@ -322,13 +336,13 @@ void mlp_grad_kernel(const float* __restrict__ w, const float* __restrict__ rows
   for (int j = 0; j < 4; ++j) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int u = 16 * t + 4 * q + j;   // hidden unit
+      const int u = hid_unit(16 * t + 4 * q + j);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) out[kOffW2 + u * kMlpHid + 16 * i + c] = acc.g2[t][i][j];
+      for (int i = 0; i < 4; ++i) out[kOffW2 + u * kMlpHid + hid_unit(16 * i + c)] = acc.g2[t][i][j];
       if (c < kMlpIn) out[kOffW1 + u * kMlpIn + c] = acc.g1[t][j];
       if (c == kMlpIn) out[kOffB1 + u] = acc.g1[t][j];
       if (c == 0) out[kOffB2 + u] = acc.b2[t][j];
-      if (q == 0) out[kOffW3 + j * kMlpHid + 16 * t + c] = acc.g3[t][j];
+      if (q == 0) out[kOffW3 + j * kMlpHid + hid_unit(16 * t + c)] = acc.g3[t][j];
     }
     if (lane == 0) out[kOffB3 + j] = acc.b3[j];
   }

@@ -351,6 +351,13 @@ __device__ __forceinline__ void spread_body(const SamplerArgs& a, const int inst
     float z_[D], b_[D];
     weights_at(mu, cur, z_, b_);
   }
+  // The three barriers of a transition order the shared arrays, each with one between its last read and its next
+  // write as well as between its write and its reads:
+  //   xbuf: written before the first, read between first and second;
+  //   term: factor 0 written before the first, 1 to 5 between first and second, read between second and third;
+  //   wbuf: written between first and second, read between second and third;
+  //   lub: written between first and second, read after the third (and so before the next first);
+  //   res: written between second and third, read after the third.
   for (int t = 1; t <= a.T; ++t) {
     // draw x' (inverse CDF; the arithmetic of draw_level)
     float kp[D], t0[D];
@@ -382,11 +389,10 @@ __device__ __forceinline__ void spread_body(const SamplerArgs& a, const int inst
     }
     put_levels(kp);
     put(0, t0);
-    if (wave == 0) {
-      const float lu = lg2((float)lubits * 5.9604644775390625e-08f);
-      lub[lane] = h == 0 ? lu : 0.f;
-    }
+    const float lu0 = lg2((float)lubits * 5.9604644775390625e-08f);   // (wave 0's)
     __syncthreads();
+    // (not earlier: a late wave still reads the last transition's until it reaches the barrier above)
+    if (wave == 0) lub[lane] = h == 0 ? lu0 : 0.f;
     float mup[D], egp[D];
     // The next transition's random words.  With one wave per SIMD (64 dimensions) their rounds are pinned
     // between the products, whose latency they fill (139 against 142 us per 100 transitions); with two

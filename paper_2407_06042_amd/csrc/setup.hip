@@ -27,8 +27,6 @@ namespace dmala {
 
 struct cd { double re, im; };
 __device__ __forceinline__ cd cadd(cd a, cd b) { return {a.re + b.re, a.im + b.im}; }
-__device__ __forceinline__ cd cmul(cd a, cd b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
-__device__ __forceinline__ cd cconjmul(cd a, cd b) { return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re}; }
 
 __device__ __forceinline__ double realeq_vec(const cd* v, int n) { return (n & 1) ? v[n >> 1].im : v[n >> 1].re; }
 
@@ -48,7 +46,7 @@ __device__ __forceinline__ cd tile_entry(const cd* X, int nb, double g, int i, i
     e = X[tile_index(nb, j, i) * 256 + 16 * c + (r ^ c)];
     e.im = -e.im;
   }
-  if constexpr (SUB) e = {(i == j && r == c ? 1.0 : 0.0) - g * e.re, -g * e.im};
+  if constexpr (SUB) e = {fma(-g, e.re, i == j && r == c ? 1.0 : 0.0), -g * e.im};
   return e;
 }
 template <bool SUB>
@@ -252,6 +250,20 @@ __device__ void pack_dense(const cd* X, int nb, double g, double c, int N, int N
   }
 }
 
+// Sum of eight partials that P consecutive lanes hold, SP each (partial i + p P in lane i): pairs of distance 4,
+// then 2, then 1, whatever P (additions commute bit for bit).
+template <int P, int SP>
+__device__ __forceinline__ cd sum8(const cd (&v)[SP]) {
+  cd s = v[0];
+  if constexpr (SP == 2) s = cadd(s, v[1]);
+#pragma unroll
+  for (int o = P >> 1; o > 0; o >>= 1) {
+    s.re += __shfl_xor(s.re, o, 64);
+    s.im += __shfl_xor(s.im, o, 64);
+  }
+  return s;
+}
+
 // LDS: a region for the matrix's tiles, the staged chunk of H (before them) and the panels of the Gauss-Jordan sweep
 // (between the two packings), then z and b, then kRedSlots partials of block_reduce and
 // the instance's constants.
@@ -301,13 +313,16 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
   // four float64 16x16x4 MFMAs per 16 x 16 tile and 4 receive antennas; each wave accumulates the tiles (i <= j)
   // assigned to it in registers across the chunks; they stay there for the inverse.  Rows past nt - 1 read whatever
   // follows in the staged rows: they only reach tile rows and columns past nt - 1, which are replaced.  z on the vector
-  // ALUs: P = BS / RMAX consecutive threads share an antenna m and split the receive
-  // antennas, then sum over those lanes.
+  // ALUs, as 8 partial sums over every eighth receive antenna, added in pairs of distance 4, 2, 1: P = BS / RMAX
+  // consecutive threads share an antenna m and take SP = 8 / P of them each, so that the sums and their
+  // order are the same for every workgroup size (as for b = M z below), and an instance's packed block is the same bytes
+  // in any launch and in a plan.
   constexpr int NW = BS / 64;
   constexpr int kNT = (RMAX + 15) / 16;                         // tile rows at nt = RMAX
   constexpr int kTPW = (kNT * (kNT + 1) / 2 + NW - 1) / NW;     // tiles per wave
   constexpr int P = BS / RMAX;
-  static_assert(P >= 1 && 16 % P == 0, "the threads of an antenna share a group of 16 lanes");
+  constexpr int SP = 8 / P;
+  static_assert(P * SP == 8 && SP <= 2, "eight partial sums, the threads of an antenna in one wavefront");
   const int ntiles = tile_count(nb);
   int m0[kTPW], m1[kTPW];
   d4 gre[kTPW], gim[kTPW];
@@ -328,7 +343,9 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
       gim[q] = d4{0.0, 0.0, 0.0, 0.0};
     }
     const int zm = tid / P, zp = tid % P;
-    cd zacc = {0.0, 0.0};
+    cd zacc[SP];
+#pragma unroll
+    for (int p = 0; p < SP; ++p) zacc[p] = {0.0, 0.0};
     // The chunk of receive antennas i0 .. i0 + kIC - 1 is loaded into registers (every load
     // issued before the first is waited for), then stored to LDS; the next chunk's loads are
     // issued before this chunk's products, so that they overlap.  Element e of a chunk:
@@ -391,22 +408,24 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
         }
       }
       if (zm < nt) {
-        for (int ii = zp; ii < ic; ii += P) {
-          const cd h = Ht[ii * ld + zm], yv = Ht[ii * ld + nt];
-          zacc.re = fma(h.re, yv.re, fma(h.im, yv.im, zacc.re));
-          zacc.im = fma(h.re, yv.im, fma(-h.im, yv.re, zacc.im));
+        for (int i8 = zp; i8 < ic; i8 += 8) {
+#pragma unroll
+          for (int p = 0; p < SP; ++p) {
+            const int ii = i8 + p * P;
+            if (ii < ic) {
+              const cd h = Ht[ii * ld + zm], yv = Ht[ii * ld + nt];
+              zacc[p].re = fma(h.re, yv.re, fma(h.im, yv.im, zacc[p].re));
+              zacc[p].im = fma(h.re, yv.im, fma(-h.im, yv.re, zacc[p].im));
+            }
+          }
         }
       }
       __syncthreads();
     }
-#pragma unroll
-    for (int o = P >> 1; o > 0; o >>= 1) {
-      zacc.re += __shfl_xor(zacc.re, o, 64);
-      zacc.im += __shfl_xor(zacc.im, o, 64);
-    }
+    const cd zs = sum8<P, SP>(zacc);
     if (zm < nt && zp == 0) {
-      z[zm] = zacc;
-      if (!isfinite(zacc.re) || !isfinite(zacc.im)) nonfinite = 1.0;
+      z[zm] = zs;
+      if (!isfinite(zs.re) || !isfinite(zs.im)) nonfinite = 1.0;
     }
     // lane l, register j of a tile's accumulator: row l / 16 + 4 j, column l % 16
     const double gamma = cst[kGamma];
@@ -576,20 +595,28 @@ __device__ __forceinline__ void setup_body(const SetupArgs& a, const int b) {
         for (int j = 0; j < 4; ++j) { const int r = lg + 4 * j; W[(wv + q * NW) * 256 + 16 * r + (r ^ lc)] = {gre[q][j], gim[q][j]}; }
       }
     __syncthreads();
-    // b = M z (the P threads of a row, summed over their lanes) and the preconditioned variance feature from M's diagonal
+    // b = M z (eight partial sums, as z's) and the preconditioned variance feature from M's diagonal
     float* afv = (float*)(frag + (size_t)(npP + kEPasses) * pass_bytes) + 2 * Npad;
     {
       const int m = tid / P, q = tid % P;
       if (m < nt) {
-        cd bp = {0.0, 0.0};
-        for (int j = q; j < nt; j += P) bp = cadd(bp, cmul(mat_entry<false>(W, nb, 0.0, m, j), z[j]));
+        cd bp[SP];
 #pragma unroll
-        for (int o = P >> 1; o > 0; o >>= 1) {
-          bp.re += __shfl_xor(bp.re, o, 64);
-          bp.im += __shfl_xor(bp.im, o, 64);
+        for (int p = 0; p < SP; ++p) bp[p] = {0.0, 0.0};
+        for (int j8 = q; j8 < nt; j8 += 8) {
+#pragma unroll
+          for (int p = 0; p < SP; ++p) {
+            const int j = j8 + p * P;
+            if (j < nt) {
+              const cd e = mat_entry<false>(W, nb, 0.0, m, j), v = z[j];
+              bp[p].re = fma(e.re, v.re, fma(-e.im, v.im, bp[p].re));
+              bp[p].im = fma(e.re, v.im, fma(e.im, v.re, bp[p].im));
+            }
+          }
         }
+        const cd bs = sum8<P, SP>(bp);
         if (q == 0) {
-          bv[m] = bp;
+          bv[m] = bs;
           const double s = cst[kStep], sigma2 = cst[kSigma2];
           if (!a.fp64) afv[2 * m] = (float)(log2(sigma2 * mat_entry<false>(W, nb, 0.0, m, m).re / (8.0 * s * s)) / 8.0);
         }

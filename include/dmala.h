@@ -293,7 +293,8 @@ typedef struct dmala_plan_s* dmala_plan;
 typedef struct { int32_t nt, nr, qam_order; } dmala_shape;
 
 /* shapes: host array [n_inst].  On success *plan is set and *workspace_bytes
- * receives the device workspace the plan needs. */
+ * receives the device workspace the plan needs (enough for any layout that
+ * dmala_plan_autotune may choose). */
 dmala_status dmala_plan_create(dmala_plan* plan, const dmala_shape* shapes, int32_t n_inst,
                                const dmala_params* params, size_t* workspace_bytes);
 

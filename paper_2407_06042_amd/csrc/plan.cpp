@@ -22,6 +22,7 @@ struct ClassInfo {
   int first = 0;          // first entry of the class in the descriptor table
   Plan pl;                // layout of this class (tile config applied)
   size_t ws_off = 0;      // offset of the class's workspace region
+  size_t room = 0;        // its size: enough for every layout the autotuner may choose
   double cost = 0.0;      // relative work estimate (LPT ordering)
   int tile_config = 0;    // 1 + sampler layout
   int cbw = 4;            // chain blocks per workgroup
@@ -30,6 +31,7 @@ struct ClassInfo {
 };
 
 constexpr int kMaxBranches = 8;
+constexpr int kTileConfigs = 10;   // explicit values of tile_config
 
 double class_cost(const dmala_shape& s, int count, const dmala_params& p) {
   // dominant per chain-iteration VALU work: proposal weights and draws over the
@@ -113,11 +115,26 @@ dmala_status class_plan(dmala_plan_s* P, ClassInfo& c) {
   p.tile_config = c.tile_config;
   p.wg_chain_blocks = c.cbw;
   const dmala_status st = make_plan(c.count, c.shape.nt, c.shape.nr, c.shape.qam_order, &p, c.pl);
+  if (st == DMALA_OK && c.room && c.pl.total > c.room)
+    return fail(DMALA_ERR_WORKSPACE, "the layout needs more than the class's part of the workspace");
   c.pl.sh.share = 1;
   c.pl.n_beside = P->n_inst;
   // (the classes share the GPU: spread over more waves when all of them together leave it room)
   if (!P->spread) c.pl.sh.spread = 0;
   return st;
+}
+
+// Bytes of a class's workspace region: the most that any layout needs (the real-equivalent layouts' matrices take
+// twice the complex planes'), so that a tuned choice fits the workspace whose size plan creation returned.
+size_t class_room(const dmala_plan_s* P, const ClassInfo& c) {
+  size_t room = c.pl.total;
+  dmala_params p = P->params;
+  for (int tc = 1; tc <= kTileConfigs; ++tc) {
+    Plan pl;
+    p.tile_config = tc;
+    if (make_plan(c.count, c.shape.nt, c.shape.nr, c.shape.qam_order, &p, pl) == DMALA_OK) room = std::max(room, pl.total);
+  }
+  return room;
 }
 
 // Assign classes (already in decreasing cost order) to graph branches, each to the
@@ -468,6 +485,7 @@ dmala_status dmala_plan_create(dmala_plan* plan, const dmala_shape* shapes, int3
       delete P;
       return st;
     }
+    c.room = class_room(P, c);
     P->classes.push_back(c);
   }
   double load = 0.0;
@@ -484,7 +502,7 @@ dmala_status dmala_plan_create(dmala_plan* plan, const dmala_shape* shapes, int3
     c.first = (int)table.size();
     for (int b : groups[std::make_tuple(c.shape.nt, c.shape.nr, c.shape.qam_order)]) table.push_back(d[b]);
     c.ws_off = ws;
-    ws = round_up(ws + c.pl.total, 256);
+    ws = round_up(ws + c.room, 256);
   }
   P->ws_total = ws;
   assign_branches(P);
@@ -556,7 +574,7 @@ dmala_status dmala_plan_autotune(dmala_plan P, const void* H, const void* y, con
     }
     double best = INFINITY;
     ClassInfo best_c = c;
-    for (int tc = 1; tc <= 10; ++tc) {
+    for (int tc = 1; tc <= kTileConfigs; ++tc) {
       for (int cb : {1, 2, 4}) {
         ClassInfo t = c;
         t.tile_config = tc;

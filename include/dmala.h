@@ -304,7 +304,8 @@ dmala_status dmala_plan_execute(dmala_plan plan, const void* H, const void* y, c
                                 dmala_stream_t stream);
 
 /* Time every admissible (layout, workgroup chain blocks) candidate of every
- * class on the given inputs and keep the fastest per class; when cache_path is
+ * class, and in a small plan (its classes spread over more waves, see tile_config) the
+ * class's own choice, on the given inputs and keep the fastest per class; when cache_path is
  * non-NULL, read earlier results from it first (classes already present are not
  * re-timed) and write the updated table back (JSON).  Synchronises `stream`. */
 dmala_status dmala_plan_autotune(dmala_plan plan, const void* H, const void* y, const void* sigma2,

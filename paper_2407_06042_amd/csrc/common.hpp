@@ -227,6 +227,8 @@ size_t sampler_lds_bytes(const Shape& sh);
 bool sampler_cfg_valid(const Shape& sh, int cfg);
 int sampler_default_cfg(const Shape& sh);
 double sampler_load(const Shape& sh, int n_inst);
+// The shape's launch takes the spread kernels.
+bool sampler_spreads(const Shape& sh);
 // Threads, chunk, sums' order and groups for a shape with C chains in a launch of n_inst instances.
 void estimate_shape(EstArgs* ea, int nt, int nr, int M, int N, int C, bool fp64, int n_inst);
 

@@ -40,10 +40,13 @@ double class_cost(const dmala_shape& s, int count, const dmala_params& p) {
   return (double)count * p.n_chains * std::max(1, p.n_iters) * (N * (Q + 20.0) + N * N / 64.0);
 }
 
-std::string class_key(const dmala_shape& s, const dmala_params& p) {
-  char buf[160];
-  snprintf(buf, sizeof buf, "nt=%d,nr=%d,M=%d,C=%d,T=%d,prec=%d,prop=%d", s.nt, s.nr, s.qam_order, p.n_chains,
-           p.n_iters, (int)p.precision, (int)p.proposal);
+// spread: the class's own choice is a spread kernel (a small plan): entries apart from those of larger plans, whose
+// layouts lose to it and which it would not suit.
+constexpr const char* kSpreadKey = ",spread";
+std::string class_key(const dmala_shape& s, const dmala_params& p, bool spread) {
+  char buf[176];
+  snprintf(buf, sizeof buf, "nt=%d,nr=%d,M=%d,C=%d,T=%d,prec=%d,prop=%d%s", s.nt, s.nr, s.qam_order, p.n_chains,
+           p.n_iters, (int)p.precision, (int)p.proposal, spread ? kSpreadKey : "");
   return buf;
 }
 
@@ -395,6 +398,7 @@ dmala_status build_graph(dmala_plan_s* P, const void* H, const void* y, const vo
 
 // Minimal reader/writer of the autotune cache:
 // {"entries": [{"key": "...", "tile_config": 3, "wg_chain_blocks": 4, "ms": 1.25}, ...]}
+// (tile_config 0, a class's own choice, only under a key of a small plan)
 struct CacheEntry {
   int tile_config, cbw;
   double ms;
@@ -422,7 +426,9 @@ std::map<std::string, CacheEntry> read_cache(const char* path) {
     if (a != std::string::npos) ce.tile_config = atoi(rest.c_str() + rest.find(':', a) + 1);
     if (b != std::string::npos) ce.cbw = atoi(rest.c_str() + rest.find(':', b) + 1);
     if (c != std::string::npos) ce.ms = atof(rest.c_str() + rest.find(':', c) + 1);
-    if (ce.tile_config > 0) m[key] = ce;
+    const size_t ns = strlen(kSpreadKey);
+    const bool own = key.size() > ns && key.compare(key.size() - ns, ns, kSpreadKey) == 0 && a != std::string::npos;
+    if (ce.tile_config > 0 || (own && ce.tile_config == 0)) m[key] = ce;
     pos = end == std::string::npos ? txt.size() : end;
   }
   return m;
@@ -560,7 +566,12 @@ dmala_status dmala_plan_autotune(dmala_plan P, const void* H, const void* y, con
   if ((e = hipEventCreate(&e0)) != hipSuccess || (e = hipEventCreate(&e1)) != hipSuccess) return hip_fail(e, "event create");
   dmala_status st = DMALA_OK;
   for (auto& c : P->classes) {
-    const std::string k = class_key(c.shape, P->params);
+    // the class's own choice: a candidate where it is none of the layouts below
+    ClassInfo own = c;
+    own.tile_config = P->params.tile_config;
+    own.cbw = P->params.wg_chain_blocks;
+    const bool spread = class_plan(P, own) == DMALA_OK && sampler_spreads(own.pl.sh);
+    const std::string k = class_key(c.shape, P->params, spread);
     auto it = cache.find(k);
     if (it != cache.end()) {
       ClassInfo t = c;
@@ -574,7 +585,27 @@ dmala_status dmala_plan_autotune(dmala_plan P, const void* H, const void* y, con
     }
     double best = INFINITY;
     ClassInfo best_c = c;
-    for (int tc = 1; tc <= kTileConfigs; ++tc) {
+    auto consider = [&](ClassInfo& t) {
+      double ms_best = INFINITY;
+      for (int rep = 0; rep < 3; ++rep) {
+        (void)hipEventRecord(e0, s);
+        st = enqueue(H, y, sigma2, t.count, t.pl, &P->params, nullptr, P->desc_dev + t.first,
+                     (unsigned char*)workspace + t.ws_off, nullptr, nullptr, nullptr, s);
+        if (st != DMALA_OK) return;
+        (void)hipEventRecord(e1, s);
+        if ((e = hipEventSynchronize(e1)) != hipSuccess) { st = hip_fail(e, "autotune run"); return; }
+        float ms = 0.f;
+        (void)hipEventElapsedTime(&ms, e0, e1);
+        if (rep > 0) ms_best = std::min(ms_best, (double)ms);
+      }
+      if (ms_best < best) {
+        best = ms_best;
+        best_c = t;
+        best_c.tuned_ms = ms_best;
+      }
+    };
+    if (spread) consider(own);
+    for (int tc = 1; tc <= kTileConfigs && st == DMALA_OK; ++tc) {
       for (int cb : {1, 2, 4}) {
         ClassInfo t = c;
         t.tile_config = tc;
@@ -584,26 +615,9 @@ dmala_status dmala_plan_autotune(dmala_plan P, const void* H, const void* y, con
         // that launch the same configuration
         if ((tc == 5 || tc == 7 || tc == 9) && cb != 4) continue;
         if ((tc == 4 || tc == 6 || tc == 8) && cb == 4) continue;
-        double ms_best = INFINITY;
-        for (int rep = 0; rep < 3; ++rep) {
-          (void)hipEventRecord(e0, s);
-          st = enqueue(H, y, sigma2, t.count, t.pl, &P->params, nullptr, P->desc_dev + t.first,
-                       (unsigned char*)workspace + t.ws_off, nullptr, nullptr, nullptr, s);
-          if (st != DMALA_OK) break;
-          (void)hipEventRecord(e1, s);
-          if ((e = hipEventSynchronize(e1)) != hipSuccess) { st = hip_fail(e, "autotune run"); break; }
-          float ms = 0.f;
-          (void)hipEventElapsedTime(&ms, e0, e1);
-          if (rep > 0) ms_best = std::min(ms_best, (double)ms);
-        }
+        consider(t);
         if (st != DMALA_OK) break;
-        if (ms_best < best) {
-          best = ms_best;
-          best_c = t;
-          best_c.tuned_ms = ms_best;
-        }
       }
-      if (st != DMALA_OK) break;
     }
     if (st != DMALA_OK) break;
     c = best_c;

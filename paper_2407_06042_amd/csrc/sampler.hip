@@ -88,9 +88,9 @@ double sampler_load(const Shape& sh, int n_inst) {
   return 1e30;
 }
 
-// Whether a shape's chain blocks can be spread (the preconditioned float chains in the layouts above).
-static bool spreadable(const Shape& sh) {
-  return !sh.fp64 && !sh.lrn && !sh.mhgd && sh.pm != PM_NAIVE && (sh.cfg == 9 || sh.cfg == 7 || (sh.cfg == 0 && sh.N > 16));
+// (the preconditioned float chains in the layouts above can be spread)
+bool sampler_spreads(const Shape& sh) {
+  return sh.spread && !sh.fp64 && !sh.lrn && !sh.mhgd && sh.pm != PM_NAIVE && (sh.cfg == 9 || sh.cfg == 7 || (sh.cfg == 0 && sh.N > 16));
 }
 
 hipError_t launch_sampler(const Shape& sh, const SamplerArgs& a, bool eval, hipStream_t s, const Persist* p, int gn,
@@ -110,7 +110,7 @@ hipError_t launch_sampler(const Shape& sh, const SamplerArgs& a, bool eval, hipS
     }
     return hipErrorInvalidValue;
   }
-  if (sh.spread && spreadable(sh) && !eval) {
+  if (sampler_spreads(sh) && !eval) {
     switch (sh.pm) {
       case PM_F16X2: return launch_spread_f16x2(sh, a, s, p, gn, cfg);
       case PM_F16X1: return launch_spread_f16x1(sh, a, s, p, gn, cfg);

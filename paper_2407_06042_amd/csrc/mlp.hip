@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const float* __restric
   mlp_stage<false>(w, lds);
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = (blockIdx.x * 4 + wave) * 64 + (lane >> 4) * 16 + (lane & 15);
+  const int64_t row = ((int64_t)blockIdx.x * 4 + wave) * 64 + (lane >> 4) * 16 + (lane & 15);
   float f[kMlpIn];
 #pragma unroll
   for (int i = 0; i < kMlpIn; ++i) f[i] = row < n ? rows[(size_t)row * stride + i] : 0.f;
@@ -58,9 +58,11 @@ static_assert(kMlpParams + 1 <= kPart, "partial record");
 constexpr int kW2Ld = 68;         // LDS row stride of W2 and of the transposed tiles: 16 B reads of 4 columns and
                                   // 4 B reads of 16 columns x 4 rows each touch every bank once
 
+// Tiles of n rows (any n of 32 bits: nothing here may pass 2^31).
+__host__ __device__ inline int train_tiles(int n) { return n / kTrainTile + (n % kTrainTile != 0); }
 // Workgroups of the gradient kernel for n rows (also the number of partial gradients).
 inline int train_wgs(int n) {
-  const int tiles = (n + kTrainTile - 1) / kTrainTile, wgs = (tiles + kTrainWaves - 1) / kTrainWaves;
+  const int tiles = train_tiles(n), wgs = (tiles + kTrainWaves - 1) / kTrainWaves;
   return wgs < kTrainWgs ? wgs : kTrainWgs;
 }
 
@@ -157,11 +159,11 @@ void mlp_grad_kernel(const float* __restrict__ w, const float* __restrict__ rows
   GradAcc acc;
   for_acc(acc, [](int, float) { return 0.f; });
 
-  const int tiles = (n + kTrainTile - 1) / kTrainTile;
+  const int tiles = train_tiles(n);
   // the lane's part of a row: inputs q and 4 + q, and the centre, precision, level count and target of axis q % 2
   struct RowIn { float x0, x1, mu, kap, qf; int t; };
   auto load_row = [&](int tile) {
-    const int r = tile * kTrainTile + c;
+    const int64_t r = (int64_t)tile * kTrainTile + c;   // (tiles past the end: past 2^31 where n is near it)
     const bool ok = r < n;
     const float* row = rows + (size_t)(ok ? r : 0) * kTrainRow;
     RowIn v;
@@ -399,7 +401,7 @@ dmala_status dmala_mlp_forward(const float* weights, const float* rows, int32_t 
   if (n_rows < 0) return fail(DMALA_ERR_ARG, "n_rows must be >= 0");
   if (row_stride < kMlpIn) return fail(DMALA_ERR_ARG, "row_stride must be >= %d", kMlpIn);
   if (n_rows == 0) return DMALA_OK;
-  const int blocks = (n_rows + 255) / 256;
+  const int blocks = n_rows / 256 + (n_rows % 256 != 0);
   hipLaunchKernelGGL(mlp_forward_kernel, dim3(blocks), dim3(256), mlp_lds_bytes<false>(), (hipStream_t)stream, weights, rows,
                      n_rows, row_stride, out);
   const hipError_t e = hipGetLastError();

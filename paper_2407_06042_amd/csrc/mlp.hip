@@ -212,8 +212,11 @@ void mlp_grad_kernel(const float* __restrict__ w, const float* __restrict__ rows
     const bool im = q & 1;
     const float oD = im ? out[1] : out[0], ob = im ? out[3] : out[2];
     const float ml = mup + oD, kl = kap * exp2f(fminf(fmaxf(ob, -4.f), 4.f));
-    // the largest logit is the nearest level's; lane groups q and q ^ 2 share an axis and take half its levels each
-    const float d0 = fminf(fmaxf(rintf(ml), 0.f), (float)(Q - 1)) - ml, mx = -kl * d0 * d0;
+    // the largest logit is the nearest level's, or with a negative precision the farthest one's; lane groups q and
+    // q ^ 2 share an axis and take half its levels each
+    const float top = (float)(Q - 1);
+    const float d0 = (kl < 0.f ? (ml + ml > top ? 0.f : top) : fminf(fmaxf(rintf(ml), 0.f), top)) - ml;
+    const float mx = -kl * d0 * d0;
     float Z = 0.f, Ej = 0.f, Ed2 = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {

@@ -114,3 +114,24 @@ def test_gradient_has_the_ordered_sums(seed, R):
         err = np.linalg.norm(g - go) / np.linalg.norm(go)
         print("rows %d: gradient error %.3g" % (R, err), flush=True)
         assert err < 1e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
+def test_negative_precisions():
+    """Rows whose logits grow away from the centre, by more than exp holds from the nearest level on.
+
+    The exponents reach 4 2^0.5 16^2 = 1450, where float32 steps are 1.2e-4: the weights, and with them loss and
+    gradient, within 1e-3."""
+    import torch
+    import paper_2407_06042_amd as dm
+    P, rows, tgt = _case(7, 640)
+    rows[:, 9] = -_f32(np.linspace(0.05, 4.0, len(rows)))
+    tr = dm.MlpTrainer(torch.from_numpy(ol.flatten(P).astype(np.float32)).cuda(), lr=1e-3)
+    loss = float(tr.step(torch.from_numpy(rows.astype(np.float32)).cuda(),
+                         torch.from_numpy(tgt.astype(np.int32)).cuda()).cpu().numpy()[0])
+    lo, go = _reference(P, rows, tgt)
+    g = tr.grad.cpu().numpy().astype(np.float64)
+    print("negative precisions: loss %.6g (%.6g), gradient error %.3g" % (loss, lo, np.linalg.norm(g - go) / np.linalg.norm(go)))
+    assert abs(loss - lo) < 1e-3 * max(1.0, abs(lo))
+    assert np.linalg.norm(g - go) < 1e-3 * np.linalg.norm(go)

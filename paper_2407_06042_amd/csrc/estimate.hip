@@ -436,23 +436,26 @@ __device__ __forceinline__ void estimate_d(const EstArgs& a, const int b) {
 }
 
 
-// A sum of exponentials 2^(v - mx) with its running maximum mx, values in log2 units: one exponential per
-// value (of the distance to the maximum) instead of one for the old sum and one for the value.
+// A sum of exponentials 2^(u (v - mx)) with its running maximum mx, values v in log2 units (u = 1) or natural ones
+// (u = log2(e)): one exponential per value (of the distance to the maximum) instead of one for the old sum and
+// one for the value.
 struct Lse2 {
   float mx = -INFINITY, sum = 0.f;
-  __device__ __forceinline__ void add(float v) {
-    const float d = v - mx, e = fex2(-fabsf(d));
+  __device__ __forceinline__ void add(float v, float u) {
+    const float d = v - mx, e = fex2(-u * fabsf(d));
     sum = d > 0.f ? __builtin_fmaf(sum, e, 1.f) : sum + e;
     mx = fmaxf(v, mx);
   }
   // merge another sum (either may be empty)
-  __device__ __forceinline__ void add(float omx, float osum) {
+  __device__ __forceinline__ void merge(float omx, float osum, float u) {
     if (omx == -INFINITY) return;
     const float m2 = fmaxf(mx, omx);
-    sum = sum * fex2(mx - m2) + osum * fex2(omx - m2);
+    sum = sum * fex2(u * (mx - m2)) + osum * fex2(u * (omx - m2));
     mx = m2;
   }
-  __device__ __forceinline__ float value() const { return (mx + flg2(sum)) * 0.6931471805599453f; }
+  __device__ __forceinline__ float value(float u) const {
+    return u == 1.f ? (mx + flg2(sum)) * 0.6931471805599453f : mx + flg2(sum) * 0.6931471805599453f;
+  }
 };
 
 // Threads that share a row's (or a bit's) chains: the largest power of two that keeps them within the given threads,
@@ -635,6 +638,7 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
   const int gm = tid / LM, it_row = tid - gm * LM, gl = tid / LP, it_llr = tid - gl * LP;
   const bool want_mc = a.marginals_mc != nullptr;
   Lse2 lnum, lden;
+  const R lu = mode == 1 ? kL2e : R(1);   // their units
   int cplus = 0;
   // row sums sum_c 2^(v_c(kQ) - Mx) (log2 units) with one running maximum Mx for the row: a point more than 2^-126
   // below the row's largest term underflows to zero, as it would in the normalised marginal anyway
@@ -848,28 +852,30 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
         }
       }
     }
-    // Bit LLRs (log2 units)
+    // Bit LLRs.  f stays in natural units up to its one product with (tau - 1) / tau log2(e): scaled to log2 units by
+    // itself it would be rounded once more (|f| reaches 1e5, where a rounding moves an LLR by 1e-2), and
+    // overflow from 2.4e38 on.
     if (a.llrs && it_llr < n_llr) {
       const int m = it_llr / (2 * NB), rem = it_llr - m * 2 * NB, ax = rem >= NB ? 1 : 0, bit = rem - ax * NB;
       const int mask = 1 << (NB - 1 - bit);
-      const R q2 = a2[m] * kL2e;
+      const R q2 = a2[m], cwl = cw * kL2e, itl = inv_tau * kL2e;
       // one loop per form (the form is uniform: no branch inside the chain loop)
       if (mode == 0) {
         for (int c = (gl - c0) & (GL - 1); c < ch; c += GL) {
           const f32x4 v = cm[c * nt + m];
           const uint32_t kk = __float_as_uint(v.w);
           const int k = ax ? (int)(kk >> 8) : (int)(kk & 255u);
-          const R av = (ax ? v.y : v.x) * kL2e;
+          const R av = ax ? v.y : v.x;
           // the other value of this Gray bit: changing bit j of the label flips the binary bits j..0
           const bool gb = ((k ^ (k >> 1)) & mask) != 0;
           const R d = (R)((k ^ (2 * mask - 1)) - k);
-          const R f0 = fs[c] * kL2e, dl = d * (av - q2 * d);   // F of the sample, and the move's change
-          // g = (F+ - F-) / tau; F(a) = log(1 + e^a): F(g) and F(-g) share log(1 + e^-|g|)
-          const R g = (gb ? dl : -dl) * inv_tau;
+          const R f0 = fs[c], dl = d * (av - q2 * d);   // F of the sample, and the move's change
+          // g = (F+ - F-) / tau; F(a) = log(1 + e^a): F(g) and F(-g) share log(1 + e^-|g|) (log2 units)
+          const R g = (gb ? dl : -dl) * itl;
           const R l1 = flg2(R(1) + fex2(-fabsf(g)));
           const R f1 = f0 + dl, Fp = gb ? f1 : f0, Fm = gb ? f0 : f1;
-          lnum.add(cw * Fp - (fmaxf(-g, R(0)) + l1));
-          lden.add(cw * Fm - (fmaxf(g, R(0)) + l1));
+          lnum.add(__builtin_fmaf(cwl, Fp, -(fmaxf(-g, R(0)) + l1)), R(1));
+          lden.add(__builtin_fmaf(cwl, Fm, -(fmaxf(g, R(0)) + l1)), R(1));
         }
       } else {
         for (int c = (gl - c0) & (GL - 1); c < ch; c += GL) {
@@ -879,8 +885,8 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
           if (mode == 2) {
             cplus += plus ? 1 : 0;
           } else if (!dupf[c0 + c]) {
-            if (plus) lnum.add(fs[c] * kL2e);
-            else lden.add(fs[c] * kL2e);
+            if (plus) lnum.add(fs[c], kL2e);
+            else lden.add(fs[c], kL2e);
           }
         }
       }
@@ -899,8 +905,8 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
     if (gl == 0 && it_llr < n_llr) {
       for (int g = 1; g < GL; ++g) {
         const R* q = o + (size_t)(g - 1) * 5 * n_llr + it_llr;
-        lnum.add(q[0], q[n_llr]);
-        lden.add(q[2 * n_llr], q[3 * n_llr]);
+        lnum.merge(q[0], q[n_llr], lu);
+        lden.merge(q[2 * n_llr], q[3 * n_llr], lu);
         cplus += (int)q[4 * n_llr];
       }
     }
@@ -973,10 +979,10 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
     R v;
     const R clip = a.llr_clip;
     if (mode == 0) {
-      v = lnum.value() - lden.value();
+      v = lnum.value(lu) - lden.value(lu);
     } else if (mode == 1) {
       const bool hp = lnum.mx > R(-INFINITY), hm = lden.mx > R(-INFINITY);
-      v = !hp ? -clip : (!hm ? clip : lnum.value() - lden.value());
+      v = !hp ? -clip : (!hm ? clip : lnum.value(lu) - lden.value(lu));
       v = v > clip ? clip : (v < -clip ? -clip : v);
     } else {
       const int cm_ = C - cplus;

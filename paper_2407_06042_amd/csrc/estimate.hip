@@ -439,8 +439,11 @@ __device__ __forceinline__ void estimate_d(const EstArgs& a, const int b) {
 // A sum of exponentials 2^(u (v - mx)) with its running maximum mx, values v in log2 units (u = 1) or natural ones
 // (u = log2(e)): one exponential per value (of the distance to the maximum) instead of one for the old sum and
 // one for the value.
+// The maximum starts at the lowest finite number: a value of -inf (a chain whose f overflows) then adds
+// nothing wherever it stands, where from -inf the distance would be NaN; sum is 0 as long as nothing was added.
+constexpr float kLowest = -3.402823466e38f;
 struct Lse2 {
-  float mx = -INFINITY, sum = 0.f;
+  float mx = kLowest, sum = 0.f;
   __device__ __forceinline__ void add(float v, float u) {
     const float d = v - mx, e = fex2(-u * fabsf(d));
     sum = d > 0.f ? __builtin_fmaf(sum, e, 1.f) : sum + e;
@@ -448,7 +451,6 @@ struct Lse2 {
   }
   // merge another sum (either may be empty)
   __device__ __forceinline__ void merge(float omx, float osum, float u) {
-    if (omx == -INFINITY) return;
     const float m2 = fmaxf(mx, omx);
     sum = sum * fex2(u * (mx - m2)) + osum * fex2(u * (omx - m2));
     mx = m2;
@@ -642,11 +644,12 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
   int cplus = 0;
   // row sums sum_c 2^(v_c(kQ) - Mx) (log2 units) with one running maximum Mx for the row: a point more than 2^-126
   // below the row's largest term underflows to zero, as it would in the normalised marginal anyway
+  // (from kLowest, as the bits')
   R Mx[RPT], sums[RPT][Q];
   int cnt[RPT][Q];
 #pragma unroll
   for (int r = 0; r < RPT; ++r) {
-    Mx[r] = R(-INFINITY);
+    Mx[r] = kLowest;
 #pragma unroll
     for (int j = 0; j < Q; ++j) { sums[r][j] = R(0); cnt[r][j] = 0; }
   }
@@ -926,8 +929,7 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
       for (int g = 1; g < GM; ++g) {
         const R* q = o + (size_t)(g - 1) * (2 * Q + 1) * n_rows + it_row;
         const R om = q[0], nm = fmaxf(om, Mx[0]);
-        // (a group without chains, or of infinite distance: its largest term is -inf)
-        const R sa = Mx[0] == nm ? R(1) : fex2(Mx[0] - nm), sb = om == nm ? R(1) : fex2(om - nm);
+        const R sa = fex2(Mx[0] - nm), sb = fex2(om - nm);
         Mx[0] = nm;
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
@@ -981,7 +983,7 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
     if (mode == 0) {
       v = lnum.value(lu) - lden.value(lu);
     } else if (mode == 1) {
-      const bool hp = lnum.mx > R(-INFINITY), hm = lden.mx > R(-INFINITY);
+      const bool hp = lnum.mx > kLowest, hm = lden.mx > kLowest;
       v = !hp ? -clip : (!hm ? clip : lnum.value(lu) - lden.value(lu));
       v = v > clip ? clip : (v < -clip ? -clip : v);
     } else {

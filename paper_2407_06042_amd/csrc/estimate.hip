@@ -1065,16 +1065,23 @@ static size_t estimate_lds(int nt, int nr, int Q, int N, int chunk, bool fp64) {
   return est_lds(nt, nr, Q, N, chunk, gm, gl, sh).end;
 }
 
+// LDS of a workgroup beside what est_lds counts: the static arrays, in a persistent launch the item word.
+constexpr size_t kEstStatic = 1024 + 16 + 16;
+
 // Chains per chunk: all of them where they fit 128 KiB of LDS (96 KiB with 256 or 512 threads, whose
-// workgroups share a CU); 256-thread workgroups run five per CU when their LDS fits 32 KiB, 512-thread ones two
-// per CU within 80 KiB: the smaller chunk that gets there, if it keeps at least 16 chains.
+// workgroups share a CU); a smaller chunk, of at least 16 chains, where that lets more workgroups share a CU.
+// 512-thread workgroups run two per CU within 80 KiB (with the static arrays; one of 81 KiB took, us for 4096
+// instances, 861 instead of 563 for 48x48 64-QAM and 64 chains, 1060 instead of 786 for 67x67 16-QAM).  256-thread ones run
+// four or five per CU within 32 KiB: those of the last KiB, four, are still faster so than with half the chunk or with
+// the next larger one that a limit for five would give them (34x34 4-QAM, 64 chains: 230 against 248; 45x45: 352 against
+// 433).
 static int estimate_chunk(int nt, int nr, int Q, int N, int C, bool fp64, int threads) {
   const size_t most = (!fp64 && threads == 1024 ? 128 : 96) * 1024;   // (float64: beside H)
   int ch = C;
   while (ch > 1 && (fp64 ? estimate_lds_bytes(nt, nr, N, ch) : estimate_lds(nt, nr, Q, N, ch, false)) > most)
     ch = (ch + 1) / 2;
   if (!fp64 && threads <= 512) {
-    const size_t budget = (threads == 256 ? 32 : 80) * 1024;
+    const size_t budget = threads == 256 ? 32 * 1024 : 80 * 1024 - kEstStatic;
     int c2 = ch;
     while (c2 > 16 && estimate_lds(nt, nr, Q, N, c2, false) > budget) c2 = (c2 + 1) / 2;
     if (estimate_lds(nt, nr, Q, N, c2, false) <= budget) ch = c2;

@@ -967,8 +967,9 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
   auto write_rows = [&](const Real (&k)[D], const Real (&m)[D]) {
     const int Nt = N >> 1;
     const int64_t sym0 = a.desc ? a.desc[inst].sym_off : (int64_t)inst * Nt;
+    static_assert(4 * RTA == D, "k and m hold the tiles the wave works on");
 #pragma unroll
-    for (int rt = 0; rt < RTW; ++rt)
+    for (int rt = 0; rt < RTA; ++rt)
 #pragma unroll
       for (int i2 = 0; i2 < 2; ++i2) {
         const int d0 = rt * 4 + 2 * i2;

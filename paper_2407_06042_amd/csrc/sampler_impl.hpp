@@ -211,23 +211,37 @@ __device__ __forceinline__ void level_weights(R mu, R kL, R (&e)[Q], R& base) {
   }
 }
 
+// sum += x^2 over a lane's dimensions d = 0, 1, ... (first: x of d = 0).  The sums of the chains' log ratio as fused
+// multiply-adds by name: of the two products that a sum begins with the compiler may fuse either one, and where it
+// chose differently in two forms of a kernel a decision within rounding of a tie could differ between them (and where it
+// did so for the forward and the reverse sum, a proposal of the current state had a log ratio of up to 1e-5, not 0).
+// PAIR: the second square rounded and the first one fused, otherwise the first rounded and the second fused.
+template <bool PAIR, typename R>
+__device__ __forceinline__ void add_square(int d, R x, R& first, R& sum) {
+  if (d == 0) first = x;
+  else if (d == 1) sum = PAIR ? __builtin_fmaf(first, first, x * x) : __builtin_fmaf(x, x, first * first);
+  else sum = __builtin_fmaf(x, x, sum);
+}
+// The order of the forward proposal's sum in a layout (the reverse one's and the mode offsets' are paired).
+constexpr bool forward_paired(int rtw, int wd) { return wd == 1 && rtw <= 4; }
+
 // log2 of the proposal normaliser sum_j exp2(-kL (j - mu)^2) (eq. softmax).
-// Its two parts: the weight sum Z relative to the mode (1 <= Z <= Q) and the squared
-// mode offset base, log2 normaliser = log2 Z - kL base.
+// Its two parts: the weight sum Z relative to the mode (1 <= Z <= Q) and the
+// mode offset b, log2 normaliser = log2 Z - kL b^2.
 template <int Q, int WIN, int W, bool TAB, typename R>
-__device__ __forceinline__ void norm_parts(R mu, R kL, const WinCoef& wc, R& Z, R& base) {
+__device__ __forceinline__ void norm_parts(R mu, R kL, const WinCoef& wc, R& Z, R& b) {
   // the sums start from the first weight, not from zero (0 + x is exact, and a
   // zero start would cost a separate fused multiply-add)
   if constexpr (WIN > 0) {
     // Z = 1 + F (c1 + F (c2 + F c3)) + G (c1' + G (c2' + G c3')): six fused multiply-adds, no powers
     R F, G, cu[W], cl[W], jf;
-    window_coefs<Q, W, TAB>(mu, kL, wc, F, G, cu, cl, jf, base);
+    window_coefs<Q, W, TAB>(mu, kL, wc, F, G, cu, cl, jf, b);
     const R zu = __builtin_fmaf(F, __builtin_fmaf(F, __builtin_fmaf(F, cu[2], cu[1]), cu[0]), 1.0f);
     Z = __builtin_fmaf(G, __builtin_fmaf(G, __builtin_fmaf(G, cl[2], cl[1]), cl[0]), zu);
-    base *= base;
   } else {
-    R e[Q];
+    R e[Q], base;
     level_weights<Q>(mu, kL, e, base);
+    b = mode_of<Q>(mu) - mu;
     Z = e[0];
 #pragma unroll
     for (int j = 1; j < Q; ++j) Z += e[j];
@@ -236,9 +250,9 @@ __device__ __forceinline__ void norm_parts(R mu, R kL, const WinCoef& wc, R& Z, 
 
 template <int Q, int WIN, int W, bool TAB, typename R>
 __device__ __forceinline__ R log2_norm(R mu, R kL, const WinCoef& wc) {
-  R Z, base;
-  norm_parts<Q, WIN, W, TAB>(mu, kL, wc, Z, base);
-  return lg2(Z) - kL * base;
+  R Z, b;
+  norm_parts<Q, WIN, W, TAB>(mu, kL, wc, Z, b);
+  return lg2(Z) - kL * (b * b);
 }
 
 // Inverse-CDF draw: the smallest level j with u Z < sum_{i <= j} w_i
@@ -1164,6 +1178,9 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
 #pragma unroll
       for (int rt = 0; rt < RTA; ++rt) word_block(rt, 1);
     }
+    // (add_square by name costs 0.7 % at 64x64 64-QAM, where the window's sums come out in its order already, and
+    // float64 ties are not within reach of it)
+    constexpr bool PLAIN = F64 || WIN > 0;
     for (int t = 1; t <= a.T; ++t) {
       load_ahead(0, ahead);
       if constexpr (!PIPE) {
@@ -1182,7 +1199,7 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       // 1. draw x' (padding dimensions never move) and -log q(x'|x); the plain
       // kernel's terms are collected as kL sum (x'_n - mu_n)^2 + sum lz_n
       Real kp[D];
-      Real S = 0, tq = 0;
+      Real S = 0, tq = 0, q0 = 0;
 #pragma unroll
       for (int d = 0; d < D; ++d) {
         if constexpr (MHG) {
@@ -1200,7 +1217,8 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
           const Real kd = draw_level<Q, WIN, W, TAB>(mu[d], kL, wc, w[d >> 2][d & 3], kB);
           kp[d] = valid[d] ? kd : kc[d];
           const Real t0 = Real(kp[d]) - mu[d];
-          tq += t0 * t0;
+          if constexpr (PLAIN) tq += t0 * t0;
+          else add_square<forward_paired(RTW, WD)>(d, t0, q0, tq);
         }
       }
       if constexpr (KND == 0) S = kL * tq + lzs;
@@ -1239,15 +1257,20 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
         // sum of the lane's log2 normalisers as log2 of the product of the weight sums
         // (each in [1, Q], so the product of D of them stays far inside the exponent
         // range): one logarithm per lane instead of one per dimension
-        Real tr = 0, zp = 1, bs = 0;
+        Real tr = 0, zp = 1, bs = 0, r0 = 0, b0 = 0;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-          Real Z, b2;
-          norm_parts<Q, WIN, W, TAB>(mup[d], kL, wc, Z, b2);
+          Real Z, b;
+          norm_parts<Q, WIN, W, TAB>(mup[d], kL, wc, Z, b);
           zp *= Z;
-          bs += b2;
           const Real t0 = Real(kc[d]) - mup[d];
-          tr += t0 * t0;
+          if constexpr (PLAIN) {
+            bs += b * b;
+            tr += t0 * t0;
+          } else {
+            add_square<true>(d, b, b0, bs);
+            add_square<true>(d, t0, r0, tr);
+          }
           T2 -= (Real(kp[d]) - Real(kc[d])) * (eg[d] + egp[d]);
         }
         if constexpr (HALF) {

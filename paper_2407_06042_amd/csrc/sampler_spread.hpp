@@ -8,8 +8,8 @@
 //
 // The results are bit for bit those of the base layout (RTW row tiles per wave, WD waves):
 // the contraction keeps its products and their order, every per-dimension value is computed by the
-// same functions, and the sums over a base wave's dimensions -- sequential fused multiply-adds per
-// lane -- are taken in the same sequence: the factors go through LDS, and each of the four chains of
+// same functions, and the sums over a base wave's dimensions -- fused multiply-adds per lane in a fixed
+// order (add_square) -- are taken in the same sequence: the factors go through LDS, and each of the four chains of
 // sums (forward and reverse proposal, energy, log normaliser) is run by one wave of the block.  Three
 // barriers per transition: proposed levels, factors, sums.
 //
@@ -437,11 +437,17 @@ __device__ __forceinline__ void spread_body(const SamplerArgs& a, const int inst
     for (int k = 0; k < 4 / RTW; ++k) {
       const int task = ws + k * RTW;
       float v[4 * RTW], u[4 * RTW], r;
-      if (task < 2) {
+      auto squares = [&](auto paired) {
         get(task, v);
+        float first = 0.f;
         r = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4 * RTW; ++i) r = __builtin_fmaf(v[i], v[i], r);
+        for (int i = 0; i < 4 * RTW; ++i) add_square<decltype(paired)::value>(i, v[i], first, r);
+      };
+      if (task == 0 && !forward_paired(RTW, WD)) {
+        squares(std::false_type{});
+      } else if (task < 2) {
+        squares(std::true_type{});
       } else if (task == 2) {
         get(2, v);
         get(3, u);
@@ -451,9 +457,9 @@ __device__ __forceinline__ void spread_body(const SamplerArgs& a, const int inst
       } else {
         get(4, v);
         get(5, u);
-        float z = 1.f, s = 0.f;
+        float z = 1.f, s = 0.f, u0 = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4 * RTW; ++i) { z *= v[i]; s = __builtin_fmaf(u[i], u[i], s); }
+        for (int i = 0; i < 4 * RTW; ++i) { z *= v[i]; add_square<true>(i, u[i], u0, s); }
         r = __builtin_fmaf(-s, kL, lg2(z));
       }
       res[(wd * 4 + task) * 64 + lane] = r;

@@ -460,11 +460,11 @@ struct Lse2 {
   }
 };
 
-// Threads that share a row's (or a bit's) chains: the largest power of two that keeps them within the given threads,
-// at most 8.
-__host__ __device__ inline int est_groups(int items, int threads) {
+// Threads that share a row's (or a bit's) C chains: the largest power of two that keeps them within the given threads,
+// at most 8 and one chain each.
+__host__ __device__ inline int est_groups(int items, int threads, int C) {
   int g = 1;
-  while (2 * g * items <= threads && g < 8) g *= 2;
+  while (2 * g * items <= threads && g < 8 && 2 * g <= C) g *= 2;
   return g;
 }
 
@@ -943,6 +943,7 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
   // lanes of one wavefront, so the log-sum-exp is a Q-lane butterfly
 #pragma unroll
   for (int r = 0; r < RPT; ++r) {
+    if (r && r * BS >= n_rows) break;   // (no thread has a second row)
     const int row = it_row + r * BS;
     R lv[Q];
     R mx = R(-INFINITY);
@@ -1041,27 +1042,31 @@ static bool estimate_h_in_lds(int nt, int nr, bool fp64) {
 }
 
 // Threads per workgroup: one (antenna, kI) row each, in 256, 512 or 1024 threads; 1024 whenever H is
-// read from global memory.  Launches of at most one workgroup per CU take 1024 threads, which shorten every phase but
-// the rows': 256 problems of 32x32 64-QAM, 64 chains, 47 us, 257 of them in 256 threads each 60 us.  The float64
-// path (nt <= 32) keeps 256.
-static int estimate_threads(int nt, int nr, int Q, bool fp64, int n_inst) {
+// read from global memory.  Launches of at most one workgroup per CU take 1024 threads where the phases of C chains are
+// work enough for them (us for 256 problems, 1024 threads / the shape's own: 32x32 64-QAM 64 chains 48 / 54, 24x24 16-QAM 32
+// chains 20.7 / 21.3; below, more waves only wait for one another: 16x16 16-QAM 64 chains 23.0 / 20.6, 4x4 16 chains 14.4 /
+// 12.3).  256-QAM has two rows per thread there, which spill: its line is five times as high (8x8 16 chains 25 / 16,
+// 24x24 32 chains 37 / 33, 32x32 128 chains 101 / 102).  The float64 path (nt <= 32) keeps 256.
+static int estimate_threads(int nt, int nr, int Q, int C, bool fp64, int n_inst) {
   if (fp64) return 256;
-  if (!estimate_h_in_lds(nt, nr, false) || nt * Q > 512 || n_inst <= 256) return 1024;
+  if (!estimate_h_in_lds(nt, nr, false) || nt * Q > 512) return 1024;
+  const size_t line = Q == 16 ? 1800000 : 360000;
+  if (n_inst <= 256 && (size_t)nt * nt * nr * C >= line) return 1024;
   return nt * Q > 256 ? 512 : 256;
 }
 
 // Threads that share a row's (a bit's) chains, of those that a large launch gives the shape.
-static void estimate_groups(int nt, int nr, int Q, int* gm, int* gl) {
-  const int NB = Q == 2 ? 1 : (Q == 4 ? 2 : (Q == 8 ? 3 : 4)), th = estimate_threads(nt, nr, Q, false, 1 << 30);
-  *gm = est_groups(nt * Q, th < 512 ? th : 512);
-  *gl = est_groups(nt * 2 * NB, th);
+static void estimate_groups(int nt, int nr, int Q, int C, int* gm, int* gl) {
+  const int NB = Q == 2 ? 1 : (Q == 4 ? 2 : (Q == 8 ? 3 : 4)), th = estimate_threads(nt, nr, Q, C, false, 1 << 30);
+  *gm = est_groups(nt * Q, th < 512 ? th : 512, C);
+  *gl = est_groups(nt * 2 * NB, th, C);
 }
 
-static size_t estimate_lds(int nt, int nr, int Q, int N, int chunk, bool fp64) {
+static size_t estimate_lds(int nt, int nr, int Q, int N, int C, int chunk, bool fp64) {
   const bool sh = estimate_h_in_lds(nt, nr, fp64);
   if (fp64) return estimate_lds_bytes(nt, nr, N, chunk) + (sh ? 2 * (size_t)(nt + 1) * nr * 8 + 16 : 0);
   int gm, gl;
-  estimate_groups(nt, nr, Q, &gm, &gl);
+  estimate_groups(nt, nr, Q, C, &gm, &gl);
   return est_lds(nt, nr, Q, N, chunk, gm, gl, sh).end;
 }
 
@@ -1078,13 +1083,13 @@ constexpr size_t kEstStatic = 1024 + 16 + 16;
 static int estimate_chunk(int nt, int nr, int Q, int N, int C, bool fp64, int threads) {
   const size_t most = (!fp64 && threads == 1024 ? 128 : 96) * 1024;   // (float64: beside H)
   int ch = C;
-  while (ch > 1 && (fp64 ? estimate_lds_bytes(nt, nr, N, ch) : estimate_lds(nt, nr, Q, N, ch, false)) > most)
+  while (ch > 1 && (fp64 ? estimate_lds_bytes(nt, nr, N, ch) : estimate_lds(nt, nr, Q, N, C, ch, false)) > most)
     ch = (ch + 1) / 2;
   if (!fp64 && threads <= 512) {
     const size_t budget = threads == 256 ? 32 * 1024 : 80 * 1024 - kEstStatic;
     int c2 = ch;
-    while (c2 > 16 && estimate_lds(nt, nr, Q, N, c2, false) > budget) c2 = (c2 + 1) / 2;
-    if (estimate_lds(nt, nr, Q, N, c2, false) <= budget) ch = c2;
+    while (c2 > 16 && estimate_lds(nt, nr, Q, N, C, c2, false) > budget) c2 = (c2 + 1) / 2;
+    if (estimate_lds(nt, nr, Q, N, C, c2, false) <= budget) ch = c2;
   }
   return ch;
 }
@@ -1092,7 +1097,7 @@ static int estimate_chunk(int nt, int nr, int Q, int N, int C, bool fp64, int th
 template <typename R, int Q, int BS>
 static hipError_t launch_eb(const EstArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {
   const bool sh = estimate_h_in_lds(a.nt, a.nr, sizeof(R) == 8);
-  const size_t lds = estimate_lds(a.nt, a.nr, Q, a.N, a.chunk, sizeof(R) == 8);
+  const size_t lds = estimate_lds(a.nt, a.nr, Q, a.N, a.C, a.chunk, sizeof(R) == 8);
   void (*k)(EstArgs, Persist);
   // (the smaller workgroups only run with H in LDS)
   constexpr bool kGlob = BS == 1024 || sizeof(R) == 8;
@@ -1145,7 +1150,7 @@ static hipError_t launch_r(const EstArgs& a, hipStream_t s, const Persist* p, in
 // where the chains that fit 96 KiB of LDS with 20 bytes per (chain, antenna) make at most 8 tiles for a workgroup's 16
 // waves.  (Any one order would do; changing a shape's moves its marginals by up to 1e-2 where |f| is 1e5.)
 static int estimate_res(int nt, int nr, int Q, int C, bool fp64) {
-  const int bs = estimate_threads(nt, nr, Q, fp64, 1 << 30);
+  const int bs = estimate_threads(nt, nr, Q, C, fp64, 1 << 30);
   if (fp64 || bs == 256) return 0;
   if (bs == 512) return 1;
   int ch = C;
@@ -1157,10 +1162,10 @@ static int estimate_res(int nt, int nr, int Q, int C, bool fp64) {
 
 void estimate_shape(EstArgs* ea, int nt, int nr, int M, int N, int C, bool fp64, int n_inst) {
   const int Q = M <= 4 ? 2 : (M <= 16 ? 4 : (M <= 64 ? 8 : 16));
-  ea->threads = estimate_threads(nt, nr, Q, fp64, n_inst);
+  ea->threads = estimate_threads(nt, nr, Q, C, fp64, n_inst);
   ea->res = estimate_res(nt, nr, Q, C, fp64);
   ea->chunk = estimate_chunk(nt, nr, Q, N, C, fp64, ea->threads);
-  estimate_groups(nt, nr, Q, &ea->gm, &ea->gl);
+  estimate_groups(nt, nr, Q, C, &ea->gm, &ea->gl);
 }
 
 hipError_t launch_estimate(const EstArgs& a, hipStream_t s, const Persist* p, int gn, KernelCfg* cfg) {

@@ -216,10 +216,11 @@ __device__ __forceinline__ void level_weights(R mu, R kL, R (&e)[Q], R& base) {
 // chose differently in two forms of a kernel a decision within rounding of a tie could differ between them (and where it
 // did so for the forward and the reverse sum, a proposal of the current state had a log ratio of up to 1e-5, not 0).
 // PAIR: the second square rounded and the first one fused, otherwise the first rounded and the second fused.
+// (The rounded square as a fused multiply-add to zero: as a product it cost 1 % of a single 32x32 problem.)
 template <bool PAIR, typename R>
 __device__ __forceinline__ void add_square(int d, R x, R& first, R& sum) {
   if (d == 0) first = x;
-  else if (d == 1) sum = PAIR ? __builtin_fmaf(first, first, x * x) : __builtin_fmaf(x, x, first * first);
+  else if (d == 1) sum = PAIR ? __builtin_fmaf(first, first, __builtin_fmaf(x, x, R(0))) : __builtin_fmaf(x, x, __builtin_fmaf(first, first, R(0)));
   else sum = __builtin_fmaf(x, x, sum);
 }
 // The order of the forward proposal's sum in a layout (the reverse one's and the mode offsets' are paired).

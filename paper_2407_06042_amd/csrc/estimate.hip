@@ -509,7 +509,9 @@ __host__ __device__ inline EstLds est_lds(int nt, int nr, int Q, int N, int chun
 // bits, 8k in the normalisers).  Two-pass normalisers, byte-wise levels, one row per thread whatever the shape and
 // branches inside the bits' chain loop took (us, full batches): 8x8 64-QAM 72 -> 68, 32x32 326 -> 263,
 // 64x64 947 -> 752, 128x128 256-QAM 414 -> 210.
-// RPT: marginal rows per thread (256-QAM beyond 64 antennas has twice as many rows as threads).
+// RPT: marginal rows per thread (256-QAM beyond 64 antennas has twice as many rows as threads; two rows' sums do not fit
+// the registers beside the rest, so that the other shapes have kernels of their own: 2000 problems of 40x40, 32 chains,
+// 338 us with two rows' registers, 309 in the former kernel).
 template <int Q, bool SH, int BS, int RPT>
 __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
   using R = float;
@@ -646,13 +648,14 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
   // below the row's largest term underflows to zero, as it would in the normalised marginal anyway
   // (from kLowest, as the bits')
   R Mx[RPT], sums[RPT][Q];
-  int cnt[RPT][Q];
+  uint32_t cnt[RPT][Q / 2];   // histogram: levels 2 w, 2 w + 1 in the halves of word w (at most 1024 chains)
 #pragma unroll
   for (int r = 0; r < RPT; ++r) {
     Mx[r] = kLowest;
 #pragma unroll
-    for (int j = 0; j < Q; ++j) { sums[r][j] = R(0); cnt[r][j] = 0; }
+    for (int j = 0; j < Q; ++j) { sums[r][j] = R(0); cnt[r][j >> 1] = 0u; }
   }
+  auto count = [&](int r, int j) { return (int)((cnt[r][j >> 1] >> (16 * (j & 1))) & 0xFFFFu); };
 
   for (int c0 = 0; c0 < C; c0 += CH) {
     const int ch = C - c0 < CH ? C - c0 : CH;
@@ -848,9 +851,14 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
 #pragma unroll
           for (int j = 0; j < Q; ++j) sums[r][j] = sums[r][j] * sc + w * eqs[j];
           Mx[r] = fmaxf(lm, Mx[r]);
-          if (want_mc) {
+        }
+        // (a loop of its own: the counts would take the sums' registers)
+        if (want_mc) {
+          for (int c = (gm - c0) & (GM - 1); c < ch; c += GM) {
+            const uint32_t kk = __float_as_uint(cm[c * nt + m].w), kQ = kk >> 8;
+            const uint32_t hit = (kk & 255u) == (uint32_t)(row & (Q - 1)) ? 1u << (16 * (kQ & 1u)) : 0u;
 #pragma unroll
-            for (int j = 0; j < Q; ++j) cnt[r][j] += (kI == kt && kQ == R(j)) ? 1 : 0;
+            for (int w = 0; w < Q / 2; ++w) cnt[r][w] += (kQ >> 1) == (uint32_t)w ? hit : 0u;
           }
         }
       }
@@ -922,7 +930,7 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
       R* q = o + (size_t)(gm - 1) * (2 * Q + 1) * n_rows + it_row;
       q[0] = Mx[0];
 #pragma unroll
-      for (int j = 0; j < Q; ++j) { q[(1 + j) * n_rows] = sums[0][j]; q[(1 + Q + j) * n_rows] = (R)cnt[0][j]; }
+      for (int j = 0; j < Q; ++j) { q[(1 + j) * n_rows] = sums[0][j]; q[(1 + Q + j) * n_rows] = (R)count(0, j); }
     }
     __syncthreads();
     if (gm == 0 && it_row < n_rows) {
@@ -934,7 +942,7 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
           sums[0][j] = sums[0][j] * sa + q[(1 + j) * n_rows] * sb;
-          cnt[0][j] += (int)q[(1 + Q + j) * n_rows];
+          cnt[0][j >> 1] += (uint32_t)q[(1 + Q + j) * n_rows] << (16 * (j & 1));
         }
       }
     }
@@ -975,7 +983,7 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
         }
       };
       if (a.marginals) store(a.marginals + o, [&](int j) { return lv[j] * inv; });
-      if (want_mc) store(a.marginals_mc + o, [&](int j) { return (float)cnt[r][j] / (float)C; });
+      if (want_mc) store(a.marginals_mc + o, [&](int j) { return (float)count(r, j) / (float)C; });
     }
   }
   if (a.llrs && gl == 0 && it_llr < n_llr) {
@@ -1005,19 +1013,19 @@ __device__ __forceinline__ void estimate_f(const EstArgs& a, const int b) {
 }
 
 // One instance by the path of the input type.
-template <typename R, int Q, bool SH, int BS>
+template <typename R, int Q, bool SH, int BS, int RPT>
 __device__ __forceinline__ void estimate_one(const EstArgs& a, const int b) {
   if constexpr (sizeof(R) == 8) estimate_d<Q, SH>(a, b);
-  else estimate_f<Q, SH, BS, (Q == 16 && BS == 1024 ? 2 : 1)>(a, b);
+  else estimate_f<Q, SH, BS, RPT>(a, b);
 }
 
 // Direct launch (PERS false): instance blockIdx.x.  Persistent launch: items from the list, each
 // with its class's arguments.
-template <typename R, int Q, bool SH, int BS, bool PERS = false>
+template <typename R, int Q, bool SH, int BS, bool PERS = false, int RPT = 1>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 1 : (BS == 256 && Q <= 8 && !PERS ? 5 : 4))))
 void estimate_kernel(EstArgs a, Persist p) {
   if constexpr (!PERS) {
-    estimate_one<R, Q, SH, BS>(a, blockIdx.x);
+    estimate_one<R, Q, SH, BS, RPT>(a, blockIdx.x);
   } else {
     extern __shared__ __attribute__((aligned(16))) unsigned char esm[];
     for (;;) {
@@ -1025,7 +1033,7 @@ void estimate_kernel(EstArgs a, Persist p) {
       if (it >= p.n_items) break;
       const WorkItem w = p.items[it];
       const EstArgs ca = ((const EstArgs*)p.cls)[__builtin_amdgcn_readfirstlane(w.cls)];
-      estimate_one<R, Q, SH, BS>(ca, __builtin_amdgcn_readfirstlane(w.inst));
+      estimate_one<R, Q, SH, BS, RPT>(ca, __builtin_amdgcn_readfirstlane(w.inst));
     }
     persist_done(p);
   }
@@ -1044,14 +1052,12 @@ static bool estimate_h_in_lds(int nt, int nr, bool fp64) {
 // Threads per workgroup: one (antenna, kI) row each, in 256, 512 or 1024 threads; 1024 whenever H is
 // read from global memory.  Launches of at most one workgroup per CU take 1024 threads where the phases of C chains are
 // work enough for them (us for 256 problems, 1024 threads / the shape's own: 32x32 64-QAM 64 chains 48 / 54, 24x24 16-QAM 32
-// chains 20.7 / 21.3; below, more waves only wait for one another: 16x16 16-QAM 64 chains 23.0 / 20.6, 4x4 16 chains 14.4 /
-// 12.3).  256-QAM has two rows per thread there, which spill: its line is five times as high (8x8 16 chains 25 / 16,
-// 24x24 32 chains 37 / 33, 32x32 128 chains 101 / 102).  The float64 path (nt <= 32) keeps 256.
+// chains 20.7 / 21.3, 32x32 256-QAM 64 chains 51 / 53; below, more waves only wait for one another: 16x16 16-QAM 64 chains
+// 23.0 / 20.6, 8x8 256-QAM 16 chains 17.5 / 15.6, 4x4 16-QAM 16 chains 14.4 / 12.3).  The float64 path (nt <= 32) keeps 256.
 static int estimate_threads(int nt, int nr, int Q, int C, bool fp64, int n_inst) {
   if (fp64) return 256;
   if (!estimate_h_in_lds(nt, nr, false) || nt * Q > 512) return 1024;
-  const size_t line = Q == 16 ? 1800000 : 360000;
-  if (n_inst <= 256 && (size_t)nt * nt * nr * C >= line) return 1024;
+  if (n_inst <= 256 && (size_t)nt * nt * nr * C >= 360000) return 1024;
   return nt * Q > 256 ? 512 : 256;
 }
 
@@ -1102,8 +1108,14 @@ static hipError_t launch_eb(const EstArgs& a, hipStream_t s, const Persist* p, i
   // (the smaller workgroups only run with H in LDS)
   constexpr bool kGlob = BS == 1024 || sizeof(R) == 8;
   if (!sh && !kGlob) return hipErrorInvalidConfiguration;
-  if (p || cfg) k = sh ? estimate_kernel<R, Q, true, BS, true> : estimate_kernel<R, Q, !kGlob, BS, true>;
-  else k = sh ? estimate_kernel<R, Q, true, BS> : estimate_kernel<R, Q, !kGlob, BS>;
+  auto pick = [&](auto rows) {
+    constexpr int RPT = decltype(rows)::value;
+    if (p || cfg) k = sh ? estimate_kernel<R, Q, true, BS, true, RPT> : estimate_kernel<R, Q, !kGlob, BS, true, RPT>;
+    else k = sh ? estimate_kernel<R, Q, true, BS, false, RPT> : estimate_kernel<R, Q, !kGlob, BS, false, RPT>;
+  };
+  constexpr bool kTwo = sizeof(R) == 4 && Q == 16 && BS == 1024;   // (64 antennas and fewer: a row per thread)
+  if (kTwo && a.nt * Q > BS) pick(std::integral_constant<int, kTwo ? 2 : 1>{});
+  else pick(std::integral_constant<int, 1>{});
   if (cfg) {
     cfg->k = (const void*)k;
     cfg->threads = BS;

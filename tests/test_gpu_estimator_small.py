@@ -37,3 +37,45 @@ def test_a_launch_within_the_chip_is_not_slower(nt, M, C):
     a, b = min(_time(nt, nt, M, C, 256) for _ in range(3)), min(_time(nt, nt, M, C, 257) for _ in range(3))
     print("%.1f us, of 257 %.1f" % (1e3 * a, 1e3 * b), flush=True)
     assert a < 1.08 * b
+
+
+@pytest.mark.parametrize("nt,nr,M,C,n", [(33, 33, 256, 40, 257), (64, 64, 256, 1024, 2), (65, 65, 256, 33, 257), (70, 71, 64, 20, 257),
+                                         (20, 21, 256, 100, 2), (5, 5, 4, 700, 2)])
+def test_histogram_counts(nt, nr, M, C, n):
+    """The Monte Carlo marginals are the final states' counts, one or two rows a thread, up to the largest chain count."""
+    _, a = run_gpu(W.make_batch(nt, nr, M, 14.0, n, seed=nt), n_chains=C, n_iters=2, seed=3, trace=False,
+                   outputs=("final_state", "marginals_mc"))
+    Q = int(round(M ** 0.5))
+    for i in (0, n - 1):
+        k = a["final_state"][i].reshape(C, nt, 2).astype(np.int64)
+        ref = np.stack([np.bincount(k[:, m, 0] * Q + k[:, m, 1], minlength=M) for m in range(nt)]) / np.float32(C)
+        np.testing.assert_array_equal(a["marginals_mc"][i].reshape(nt, M), ref.astype(np.float32))
+
+
+def _time_of(nt, nr, M, C, n, outputs):
+    """Median time of the estimator's kernel for n instances (no transitions)."""
+    import torch
+    import paper_2407_06042_amd as dm
+    g = torch.Generator(device="cuda").manual_seed(1)
+    H = torch.randn(n, nt, nr, dtype=torch.complex64, device="cuda", generator=g) / nr ** 0.5
+    y = torch.randn(n, nr, dtype=torch.complex64, device="cuda", generator=g)
+    d = dm.Detector(n, nt, nr, M, C, 0, 1, outputs=outputs)
+    s2 = torch.full((n,), 0.1, device="cuda")
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    for e in ev:
+        e.record()
+    ms = []
+    for _ in range(12):
+        d(H, y, s2, events=[e.cuda_event for e in ev])
+        torch.cuda.synchronize()
+        ms.append(ev[2].elapsed_time(ev[3]))
+    return float(np.median(ms[2:]))
+
+
+@pytest.mark.parametrize("nt,C,n", [(48, 32, 1000), (68, 32, 1000)])
+def test_histogram_beside_the_sums(nt, C, n):
+    """256-QAM with the Monte Carlo marginals: the counts are a few integer operations per chain beside the sums, and a
+    store (kept beside the sums in registers they took 1.8 times the time of the sums alone with two rows per thread)."""
+    a, b = (min(_time_of(nt, nt, 256, C, n, ("marginals", "best_energy") + mc) for _ in range(3)) for mc in ((), ("marginals_mc",)))
+    print("%.1f us, with the histogram %.1f" % (1e3 * a, 1e3 * b), flush=True)
+    assert b < 1.35 * a

@@ -188,4 +188,46 @@ __device__ __forceinline__ mlp_f32x4 mlp_eval4(const unsigned char* lds, uint32_
   return out;
 }
 
+// The same outputs, one antenna group after another with each layer whole.  For 4-QAM beyond 64 antennas in two fp16
+// parts, whose other registers leave no room for two groups at once (sampler, 375 problems of 85x85, 32 chains, 20
+// transitions: 1962 us in pairs, 1652 so; 300 of 128x128 1875, 1594); the larger alphabets are the faster in pairs
+// (128x128 16-QAM 1943 one by one, 1780 in pairs).
+template <bool GW1>
+__device__ __forceinline__ mlp_f32x4 mlp_eval4_single(const unsigned char* lds, uint32_t lds_off, mlp_bf16x8 x) {
+  using I = MlpImage<GW1>;
+  const int lane = threadIdx.x & 63, h = lane >> 4;
+  const float* bias = (const float*)(lds + lds_off + (size_t)I::kFrags * 1024);
+  mlp_f32x4 out = *(const mlp_f32x4*)(bias + 64);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const unsigned char* base = lds + lds_off + opaque_zero_u32() + (uint32_t)lane * 16;
+    const mlp_bf16x8 zero8 = {};
+    const mlp_bf16x8 xg = (GW1 || h == g) ? x : zero8;
+    mlp_f32x4 z1[4], z2[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const mlp_f32x4 c0 = {0.f, 0.f, 0.f, 0.f};
+      const mlp_bf16x8 w1 = *(const mlp_bf16x8*)(base + (I::kW1 + (GW1 ? 4 * g : 0) + t) * 1024);
+      z1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, xg, c0, 0, 0, 0);
+    }
+    const mlp_bf16x8 a1[2] = {relu_bf16x8(z1[0], z1[1]), relu_bf16x8(z1[2], z1[3])};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      z2[t] = *(const mlp_f32x4*)(bias + 16 * t + 4 * h);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const mlp_bf16x8 w2 = *(const mlp_bf16x8*)(base + (I::kW2 + 2 * t + k) * 1024);
+        z2[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2, a1[k], z2[t], 0, 0, 0);
+      }
+    }
+    const mlp_bf16x8 a2[2] = {relu_bf16x8(z2[0], z2[1]), relu_bf16x8(z2[2], z2[3])};
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const mlp_bf16x8 w3 = *(const mlp_bf16x8*)(base + (I::kW3 + 2 * g + s) * 1024);
+      out = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3, a2[s], out, 0, 0, 0);
+    }
+  }
+  return out;
+}
+
 }  // namespace dmala

@@ -968,7 +968,10 @@ __device__ __forceinline__ void sampler_body(const SamplerArgs& a, const int ins
       for (int i2 = 0; i2 < 2; ++i2) {
         float f[kMlpIn];
         feats(k, m, rt, i2, f);
-        const mlp_f32x4 o = mlp_eval4<mlp_gw1(WD)>(mlp_lds, mo, mlp_inputs(f[0], f[1], f[2], f[3], f[4], f[5], f[6]));
+        const mlp_bf16x8 x = mlp_inputs(f[0], f[1], f[2], f[3], f[4], f[5], f[6]);
+        mlp_f32x4 o;
+        if constexpr (Q == 2 && RT == 16 && PM == PM_F16X2) o = mlp_eval4_single<mlp_gw1(WD)>(mlp_lds, mo, x);
+        else o = mlp_eval4<mlp_gw1(WD)>(mlp_lds, mo, x);
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
           const int d = rt * 4 + 2 * i2 + p;

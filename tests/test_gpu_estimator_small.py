@@ -52,6 +52,26 @@ def test_histogram_counts(nt, nr, M, C, n):
         np.testing.assert_array_equal(a["marginals_mc"][i].reshape(nt, M), ref.astype(np.float32))
 
 
+def test_row_forms_side_by_side_in_a_plan():
+    """256-QAM classes of one and of two rows per thread, and another alphabet, in one plan's launches."""
+    import torch
+    import paper_2407_06042_amd as dm
+    shapes = [(64, 64, 256)] * 2 + [(65, 66, 256)] * 3 + [(40, 41, 256)] * 2 + [(128, 128, 256), (70, 70, 64), (5, 6, 256)]
+    C, T, seed = 40, 3, 5
+    bs = [W.make_batch(nt, nr, M, 20.0, 1, seed=i).as_precision(np.float32) for i, (nt, nr, M) in enumerate(shapes)]
+    H, y, sig = dm.pack_uneven([b.H[0] for b in bs], [b.y[0] for b in bs], np.array([b.sigma2[0] for b in bs]))
+    outs = ("symbols", "marginals", "llrs", "best_energy", "marginals_mc")
+    res = {k: v.cpu().numpy() for k, v in dm.Plan(shapes, C, T, seed, outputs=outs)(H, y, sig).items()}
+    at = dict.fromkeys(outs, 0)
+    for i, (nt, nr, M) in enumerate(shapes):
+        u = dm.Detector(1, nt, nr, M, C, T, seed, outputs=outs, counter_base=i)(*dm.device_inputs(bs[i].H, bs[i].y, bs[i].sigma2))
+        torch.cuda.synchronize()
+        for k in outs:
+            v = u[k].cpu().numpy().reshape(-1)
+            np.testing.assert_array_equal(v, res[k][at[k]:at[k] + v.size], err_msg="%s of problem %d" % (k, i))
+            at[k] += v.size
+
+
 def _time_of(nt, nr, M, C, n, outputs):
     """Median time of the estimator's kernel for n instances (no transitions)."""
     import torch
